@@ -286,7 +286,9 @@ typedef struct csl_batch_opts {
     int timeout_ms;
     int grid_size;          /* workgroups of the persistent launch; 0 = auto   */
     int use_graph;          /* 1: replay a captured hipGraph per solve          */
-    int tile_points;        /* grid points per scheduling tile (0 = 8192);
+    int tile_points;        /* grid points per scheduling tile (0 = by the
+                               batch: about one tile per workgroup and phase,
+                               4096 to 16384, for 2-D FFT systems, else 8192);
                                larger tiles mean fewer cross-workgroup
                                hand-offs, smaller ones more parallelism    */
     int lds_bytes;          /* LDS line budget per workgroup: 0 = per

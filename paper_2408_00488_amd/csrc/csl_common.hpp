@@ -99,6 +99,10 @@ struct SysDesc {
                   // a time held in LDS (lgB = 0; Tq, Tv and T hold all real
                   // parts, then all imaginary parts, each with the plane of
                   // contiguous-axis index c contiguous)
+  int ld;         // column stride of Tq, Tv and T in the team phases (the 512-thread
+                  // instances): element (row, c) at c ld + row, ld >= rows an odd
+                  // multiple of 8; lpt_* are the lines of a round there (one per
+                  // team), a chunk is a round
   int nchunk[K_NKINDS];  // LDS-sized chunks of each phase kind
   int cpt[K_NKINDS];     // chunks per tile (one scheduling unit)
   int ntile[K_NKINDS];   // ceil(nchunk / cpt)
@@ -132,6 +136,19 @@ struct SysDesc {
 };
 
 constexpr int kLanczosCap = 4096;
+
+// Team phases: LDS of the line buffers (4096 FP64 points in up to 64 lines, and
+// one 16-byte element of padding a line) and of the workgroup (the twiddles of
+// both precisions behind them), lanes per line, lines a workgroup of 512
+// threads holds, and the column stride.
+constexpr int kTeamBufBytes = 65536 + 1024;
+constexpr int kTeamLdsBytes = kTeamBufBytes + 8192;
+__host__ __device__ inline int team_lanes(int n) { return n >= 7 ? (n + 1) / 8 : 1; }
+__host__ __device__ inline int team_lines(int n) {
+  const int g = 512 / team_lanes(n);
+  return g < 64 ? g : 64;
+}
+__host__ __device__ inline int team_ld(int rows) { return (((rows + 7) / 8) | 1) * 8; }
 // Dynamic LDS of the plane-phase solver instances (the whole 160 KiB of a CU
 // less a margin for their static variables), and what a plane tile needs of
 // it: one part of the plane in the preconditioner precision (eb bytes per

@@ -31,11 +31,17 @@
 #ifndef CSL_PLANE
 #define CSL_PLANE 0
 #endif
+#ifndef CSL_TEAM
+#define CSL_TEAM 0
+#endif
 #ifndef CSL_PLANE_F64
 #define CSL_PLANE_F64 0
 #endif
 #ifndef CSL_WAVES_PER_EU
 #define CSL_WAVES_PER_EU (CSL_NT / 128)
+#endif
+#if CSL_TEAM
+#include "csl_team.hpp"
 #endif
 
 namespace csl {
@@ -1189,9 +1195,40 @@ __device__ __forceinline__ void tile_YP(const SysDesc &S, int iter, int tile, ch
 }
 #endif  // CSL_PLANE
 
+#if CSL_TEAM
+template <int D>
+__device__ __forceinline__ void team_tile(const SysDesc &S, const IOPtr &io, int kind, int iter, int tile,
+                                          char *smem, double *red, double *carry) {
+  if (kind == K_X) {
+    tile_TX<D>(S, io, iter, tile, smem, red, carry);
+  } else if (kind == K_Z) {
+    if (S.prec) tile_TZ<float, D>(S, io, iter, tile, smem, carry);
+    else tile_TZ<double, D>(S, io, iter, tile, smem, carry);
+  } else if (kind == K_PR) {
+    tile_PR<D>(S, io, tile, red);
+  } else if (D == 3 && kind == K_Y) {
+    if (S.prec) tile_TY0<float>(S, tile, smem, red, carry);
+    else tile_TY0<double>(S, tile, smem, red, carry);
+  } else {
+    if (S.prec) tile_TY<float, D>(S, kind, iter, tile, smem, red, carry);
+    else tile_TY<double, D>(S, kind, iter, tile, smem, red, carry);
+  }
+}
+#endif
+
 template <int LDSB>
 __device__ __forceinline__ void process_tile(const SysDesc &S, const IOPtr &io, int kind, int iter, int tile,
                              char *smem, double *red) {
+#if CSL_TEAM
+  __shared__ double carry[2 * (NT / 64)];
+#if CSL_2D_FFT_ONLY
+  team_tile<2>(S, io, kind, iter, tile, smem, red, carry);
+#else
+  if (S.d == 3) team_tile<3>(S, io, kind, iter, tile, smem, red, carry);
+  else team_tile<2>(S, io, kind, iter, tile, smem, red, carry);
+#endif
+  return;
+#else
 #if CSL_2D_FFT_ONLY
   const bool d3 = false;
   const bool g = false;
@@ -1283,6 +1320,7 @@ __device__ __forceinline__ void process_tile(const SysDesc &S, const IOPtr &io, 
       }
       break;
   }
+#endif  // CSL_TEAM
 }
 
 #if !CSL_SOLVE_ONLY
@@ -1594,7 +1632,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
   __shared__ double red[NT / 64];
   __shared__ int sh_s, sh_tile, sh_kind, sh_iter, sh_last;
   const int tid = threadIdx.x;
+#if CSL_TEAM
+  team_stage_twiddles(smem);
+#else
   twiddle_cache_reset();
+#endif
   int cur = blockIdx.x % nsys;
   const long long t0 = wall_clock64();
   int backoff = 0;
@@ -2234,6 +2276,10 @@ hipError_t launch_solve(const SysDesc *dsys, const IOPtr *dio, IOPtr io0, int ns
   (void)smem;
   hipLaunchKernelGGL(solve_kernel<65536>, dim3(grid), dim3(NT), kPlaneLdsBytes, s, dsys, dio, io0,
                      nsys, P, G);
+#elif CSL_TEAM
+  (void)smem;
+  hipLaunchKernelGGL(solve_kernel<65536>, dim3(grid), dim3(NT), kTeamLdsBytes, s, dsys, dio, io0,
+                     nsys, P, G);
 #else
   if (smem <= 32768)
     hipLaunchKernelGGL(solve_kernel<32768>, dim3(grid), dim3(NT), 32768 + tw_lds_bytes(32768), s, dsys, dio,
@@ -2250,6 +2296,10 @@ hipError_t solve_occupancy(size_t smem, int *blocks_per_cu) {
   (void)smem;
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, solve_kernel<65536>, NT,
                                                       kPlaneLdsBytes);
+#elif CSL_TEAM
+  (void)smem;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, solve_kernel<65536>, NT,
+                                                      kTeamLdsBytes);
 #else
   if (smem <= 32768)
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, solve_kernel<32768>, NT,

@@ -192,6 +192,58 @@ void plane_tiling(SysDesc &h) {
   }
   h.maxtile = mx;
 }
+// Rewrite a tiling for the team phases of the 512-thread instances (the FFT on
+// every axis): a round holds one line per team, a chunk is a round.  te > 0:
+// rounds of te FFT elements, as the other tilings take it.  target > 0: rounds
+// of fewer lines while that gives at most `target` of them (a solve that has
+// the device to itself spreads its lines over the CUs), down to one line per
+// wave.
+void team_tiling(SysDesc &h, int te, int target) {
+  auto round_lines = [&](int n, long long lines) {
+    int g = team_lines(n);
+    if (te > 0) {
+      int want = 1;
+      while (want * 2 <= te / (2 * (n + 1))) want *= 2;
+      return std::min(g, want);
+    }
+    const int lo = std::max(1, 64 / team_lanes(n));
+    while (g > lo && (lines + g / 2 - 1) / (g / 2) <= target) g /= 2;
+    return g;
+  };
+  const int nl = h.n[h.d - 1];
+  h.ld = team_ld(h.rows);
+  h.lpt_x = h.lpt_z = round_lines(nl, h.rows);
+  h.nchunk[K_X] = h.nchunk[K_Z] = (h.rows + h.lpt_x - 1) / h.lpt_x;
+  if (h.d == 3) {
+    const long long l1 = (long long)h.n[2] * h.n[0], l0 = (long long)h.n[2] * h.n[1];
+    h.lpt_s[1] = round_lines(h.n[1], l1);
+    h.lpt_s[0] = round_lines(h.n[0], l0);
+    h.nchunk[K_Y1] = h.nchunk[K_Y1I] = (int)((l1 + h.lpt_s[1] - 1) / h.lpt_s[1]);
+    h.nchunk[K_Y] = h.n[2] * ((h.n[1] + h.lpt_s[0] - 1) / h.lpt_s[0]);
+  } else {
+    h.lpt_s[0] = round_lines(h.n[0], nl);
+    h.nchunk[K_Y] = (nl + h.lpt_s[0] - 1) / h.lpt_s[0];
+  }
+  h.maxtile = 0;
+  for (int k = 0; k < K_NKINDS; ++k) {
+    h.cpt[k] = 1;
+    h.ntile[k] = h.nchunk[k];
+    h.maxtile = std::max(h.maxtile, h.ntile[k]);
+  }
+}
+// Tiles of the finest team tiling (rounds of one line).
+int team_max_tiles(const SysDesc &h) {
+  const int nl = h.n[h.d - 1];
+  int mx = std::max(h.rows, nl);
+  if (h.d == 3) mx = std::max(mx, nl * std::max(h.n[0], h.n[1]));
+  return mx;
+}
+// Entries of Tq, Tv and T: column-blocked, rows x ceil(n_last / B) B with B <=
+// 64, or the team phases' columns of stride team_ld(rows).
+size_t column_entries(const SysDesc &h) {
+  const size_t nl = (size_t)h.n[h.d - 1];
+  return std::max((size_t)h.rows * (nl + 63), (size_t)team_ld(h.rows) * nl);
+}
 // Workgroup size for a request (0 = the larger one where allowed).
 int resolve_wg(int block_threads, bool wg512_ok) {
   if (block_threads == 256) return 256;
@@ -224,6 +276,7 @@ struct csl_problem_s {
   double wall_khz = 0.0;
   SysDesc h{};
   SysDesc *d_desc = nullptr;
+  SysDesc *d_desc0 = nullptr;   // h0: the stand-alone P^{-1} passes
   void *mem = nullptr;
   Glob *glob = nullptr;
   double *stats = nullptr;
@@ -504,7 +557,7 @@ void free_problem(csl_problem p) {
 // forward (3-D), 2 axis 0 with the mode scaling, 3 axis-1 inverse (3-D),
 // 4 rows inverse.
 hipError_t launch_pinv_all(csl_problem p, const double2 *x, double2 *y, hipStream_t s) {
-  const SysDesc &h = p->h;
+  const SysDesc &h = p->h0;   // the creation-time tiling, whatever the solver's schedule
   const int nrow = (h.rows + h.lpt_z - 1) / h.lpt_z;
   const int pass[5] = {0, 1, 2, 3, 4};
   for (int k = 0; k < 5; ++k) {
@@ -514,7 +567,7 @@ hipError_t launch_pinv_all(csl_problem p, const double2 *x, double2 *y, hipStrea
                    : pass[k] == 2             ? h.nchunk[K_Y]
                    : pass[k] == 1             ? h.nchunk[K_Y1]
                                               : h.nchunk[K_Y1I];
-    const hipError_t e = wg256::launch_pinv_pass(p->d_desc, h.d, h.prec, pass[k], nt, p->smem, x, y, s);
+    const hipError_t e = wg256::launch_pinv_pass(p->d_desc0, h.d, h.prec, pass[k], nt, p->smem0, x, y, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -544,6 +597,10 @@ csl_status configure_single(csl_problem p, int tile_points, int lds_bytes, int b
   // every tile of every phase owns a partial-sum slot
   if (h.maxtile > p->part_cap) return fail(CSL_ERR_ARG, "chunking exceeds the partial-sum slots");
   const int wg = resolve_wg(block_threads, p->wg512_ok);
+  if (wg == 512) {
+    team_tiling(h, p->single_te, p->cus);
+    sm = 65536;
+  }
   int bpc = 0;
   HIPCHK(solve_occupancy_wg(wg, p->h0.d == 2, has_gemm16(p->h0), p->h0.prec == 0, sm, &bpc));
   const int cap = std::max(1, bpc) * p->cus;
@@ -552,6 +609,7 @@ csl_status configure_single(csl_problem p, int tile_points, int lds_bytes, int b
   int mt = 1;
   for (int k = 0; k < K_NKINDS; ++k) mt = std::max(mt, h.ntile[k]);
   HIPCHK(hipMemcpyAsync(p->d_desc, &h, sizeof(SysDesc), hipMemcpyHostToDevice, s));
+  HIPCHK(hipMemcpyAsync(p->d_desc0, &p->h0, sizeof(SysDesc), hipMemcpyHostToDevice, s));
   HIPCHK(hipStreamSynchronize(s));
   p->h = h;
   p->smem = sm;
@@ -641,7 +699,8 @@ csl_status configure_batch(csl_batch b, int tile_points, int lds_bytes, int bloc
   b->graph = nullptr;
   std::vector<SysDesc> descs(b->count);
   size_t smem = 0;
-  const bool plane = resolve_wg(block_threads, b->wg512_ok) == 1024;
+  const int wg = resolve_wg(block_threads, b->wg512_ok);
+  const bool plane = wg == 1024;
   for (int i = 0; i < b->count; ++i) {
     const csl_problem p = b->probs[i];
     descs[i] = p->h0;
@@ -656,6 +715,10 @@ csl_status configure_batch(csl_batch b, int tile_points, int lds_bytes, int bloc
       // a larger budget only lengthens the chunks: chunk counts (and with
       // them the partial-sum slots each problem allocated) can only shrink
       choose_tiles(descs[i], p->tile_elems, lds_bytes, &sm);
+    }
+    if (wg == 512) {
+      team_tiling(descs[i], 0, 0);
+      sm = 65536;
     }
     descs[i].info = b->d_info + i;
     set_tile_points(descs[i], tile_points);
@@ -691,6 +754,22 @@ csl_status configure_batch(csl_batch b, int tile_points, int lds_bytes, int bloc
   (void)hipStreamDestroy(cs);
   if (!ok) return fail(CSL_ERR_HIP, "hipGraph capture of the batched solve failed");
   return CSL_OK;
+}
+
+// Tile size of a batch that asks for none.  The 2-D team phases run one
+// workgroup per CU, and every tile costs about 10 us of hand-off, so a phase of
+// the whole batch is cut into about one tile per workgroup, between 4096 points
+// (a round of rows) and 16384 (longer tiles lengthen the chains of the large
+// systems): 64 systems of 63^2 to 511^2 points 17.7 ms with 16384 points,
+// 20.8 with 8192, 18.3 with 24576; 64 of 255^2 13.9, 16.1 and 16.3 ms; 16 of
+// 255^2 1.9 ms with 4096, 2.1 with 8192, 3.1 with 16384.  Other batches keep
+// 8192.
+int default_tile_points(csl_batch b, int wg) {
+  if (wg != 512 || !b->all2d) return 8192;
+  long long pts = 0;
+  for (csl_problem p : b->probs) pts += p->h.M;
+  const long long per = pts / std::max(1, b->probs[0]->cus);
+  return (int)std::min<long long>(16384, std::max<long long>(4096, per));
 }
 
 // Geometry of a system from the caller's grid: sizes, strides, mesh widths,
@@ -822,8 +901,7 @@ static csl_status create_problem_impl(const csl_grid *grid, const double *a_noda
 
   // one allocation for the coefficient copy, tables and workspaces
   const size_t vec = align256(sizeof(double2) * (size_t)h.M);
-  // column-blocked vectors: rows x ceil(n_last / B) B entries, B <= 64
-  const size_t Mb = (size_t)h.rows * (size_t)(h.n[h.d - 1] + 63);
+  const size_t Mb = column_entries(h);
   const size_t vecb = align256(sizeof(double2) * Mb);
   const size_t tsz = align256(Mb * (h.prec ? 8 : 16));
   const int nmu = h.n[0] + h.n[1] + h.n[2];
@@ -852,11 +930,12 @@ static csl_status create_problem_impl(const csl_grid *grid, const double *a_noda
     choose_tiles(t, kSmallChunkElems[0], 0, &sm_t);
     part_cap = std::max(part_cap, t.maxtile);
   }
-  const size_t o_part = take(sizeof(double) * part_cap);
+  const size_t o_part = take(sizeof(double) * std::max(part_cap, team_max_tiles(h)));
   const size_t o_ctl = take(sizeof(Ctl));
   const size_t o_info = take(sizeof(DevInfo));
   const size_t o_glob = take(sizeof(Glob));
   const size_t o_desc = take(sizeof(SysDesc));
+  const size_t o_desc0 = take(sizeof(SysDesc));
   const size_t o_stats = take(sizeof(double) * 4);
   const size_t o_spart = take(sizeof(double) * 4 * p->stats_nblk);
   const size_t o_ytmp = take(vec);
@@ -900,6 +979,7 @@ static csl_status create_problem_impl(const csl_grid *grid, const double *a_noda
   p->glob = (Glob *)(base + o_glob);
   p->part_cap = part_cap;
   p->d_desc = (SysDesc *)(base + o_desc);
+  p->d_desc0 = (SysDesc *)(base + o_desc0);
   p->stats = (double *)(base + o_stats);
   p->stats_part = (double *)(base + o_spart);
   p->ytmp = (double2 *)(base + o_ytmp);
@@ -1239,7 +1319,7 @@ csl_status minres_solve_noalloc(const csl_grid *grid, const double *a_nodal, dou
   // coefficient copy, the adjoint buffers and the sine matrices
   const int stats_nblk = std::min(1024, (h.M + kAuxThreads - 1) / kAuxThreads);
   const size_t vec = align256(sizeof(double2) * (size_t)h.M);
-  const size_t Mb = (size_t)h.rows * (size_t)(h.n[h.d - 1] + 63);
+  const size_t Mb = column_entries(h);
   const size_t vecb = align256(sizeof(double2) * Mb);
   const size_t tsz = align256(Mb * (h.prec ? 8 : 16));
   const int nmu = h.n[0] + h.n[1] + h.n[2];
@@ -1255,7 +1335,7 @@ csl_status minres_solve_noalloc(const csl_grid *grid, const double *a_nodal, dou
   const size_t o_glob = take(sizeof(Glob));
   const size_t o_stats = take(sizeof(double) * 4);
   const size_t o_spart = take(sizeof(double) * 4 * stats_nblk);
-  const size_t o_part = take(sizeof(double) * std::max(1, h.maxtile));
+  const size_t o_part = take(sizeof(double) * std::max(h.maxtile, team_max_tiles(h)));
   const size_t o_lz = take(sizeof(double) * (2 * kLanczosCap + 1));
   const size_t o_mu = take(sizeof(double) * nmu);
   const size_t o_muf = take(sizeof(float) * nmu);
@@ -1354,6 +1434,7 @@ csl_status minres_solve_noalloc(const csl_grid *grid, const double *a_nodal, dou
   int bpc = 0;
   HIPCHK(solve_occupancy_wg(wg, h.d == 2, false, false, smem, &bpc));
   const int cap = std::max(1, bpc) * sd.cus;
+  team_tiling(h, o.tile_elems, sd.cus);
   set_tile_points(h, (int)std::min<long long>(1 << 30, h.M / cap));
   int mt = 1;
   for (int k = 0; k < K_NKINDS; ++k) mt = std::max(mt, h.ntile[k]);
@@ -1440,7 +1521,7 @@ csl_status problem_tune(csl_problem p, const double *f, double *z, csl_batch_tun
       if (wg == 512 && !w512) continue;
       if (wg == 1024 && !w1024) continue;
       for (int lds : {32768, 65536}) {
-        if (wg == 1024 && lds != 65536) continue;   // the plane instance's own budget
+        if (wg != 256 && lds != 65536) continue;   // the instance's own budget
         std::vector<long long> tps;
         for (long long tp : {0LL, 1LL, per_wg / 2, per_wg * 2, per_wg * 4, per_wg * 8, 4096LL, 8192LL})
           if (tp >= 0 && tp <= (1LL << 30) && std::find(tps.begin(), tps.end(), tp) == tps.end())
@@ -1453,7 +1534,7 @@ csl_status problem_tune(csl_problem p, const double *f, double *z, csl_batch_tun
         for (int te : kSmallChunkElems)
           for (long long tp : {0LL, 1LL, per_wg})
             if (!((int)tp == tp0 && wg == wg0 && te == te0 && m == mask0))
-              cands.push_back({(int)tp, 32768, wg, te, m});
+              cands.push_back({(int)tp, wg == 256 ? 32768 : 65536, wg, te, m});
     }
   }
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1634,8 +1715,9 @@ csl_status batch_create(const csl_problem *problems, int count, const csl_batch_
         hipSuccess)
       return cleanup(CSL_ERR_HIP, "hipMemcpy of the adjoint pointers failed");
   }
-  const csl_status st = configure_batch(b, o.tile_points > 0 ? o.tile_points : 8192,
-                                        o.lds_bytes, o.block_threads, b->use_graph);
+  const int tp = o.tile_points > 0 ? o.tile_points
+                                   : default_tile_points(b, resolve_wg(o.block_threads, b->wg512_ok));
+  const csl_status st = configure_batch(b, tp, o.lds_bytes, o.block_threads, b->use_graph);
   if (st != CSL_OK) {
     const std::string msg = g_err;
     return cleanup(st, msg);
@@ -1777,8 +1859,10 @@ csl_status batch_tune(csl_batch b, const double *const *f, double *const *z,
     if (wg == 512 && !b->wg512_ok) continue;
     if (wg == 1024 && !b->plane_ok) continue;
     for (int lds : {32768, 65536}) {
-      if (wg == 1024 && lds != 65536) continue;   // the plane instance's own budget
-      for (int tp : {6144, 8192, 12288, 16384, 24576})
+      if (wg != 256 && lds != 65536) continue;   // the instance's own budget
+      std::vector<int> tps = {6144, 8192, 12288, 16384, 24576};
+      if (wg == 512) tps.insert(tps.end(), {1024, 2048, 4096, 32768, 49152});
+      for (int tp : tps)
         if (!(tp == tp0 && lds == lds0 && wg == wg0)) cands.push_back({tp, lds, wg});
     }
   }
