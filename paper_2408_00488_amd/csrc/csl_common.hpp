@@ -29,16 +29,16 @@ enum Kind : int {
   K_DONE = 15
 };
 
-// Ticket word of a system: [iter:24 | owned:1 | kind:7 | next tile:32]; owned
-// marks a phase whose first tiles belong to the workgroups of a fully
-// resident single-system grid (see the solver's scheduler).
+// Ticket word of a system: [iter:24 | flat:1 | kind:7 | next tile:32]; flat
+// marks the phase from which the workgroups of a fully resident
+// single-system grid go on without claims (see the solver's flat solve).
 __host__ __device__ inline uint64_t make_word(int iter, int kind) {
   return ((uint64_t)(uint32_t)iter << 40) | ((uint64_t)(uint32_t)kind << 32);
 }
-constexpr uint64_t kWordOwned = 1ull << 39;
+constexpr uint64_t kWordFlat = 1ull << 39;
 __host__ __device__ inline int word_iter(uint64_t w) { return (int)(w >> 40); }
 __host__ __device__ inline int word_kind(uint64_t w) { return (int)((w >> 32) & 0x7f); }
-__host__ __device__ inline bool word_owned(uint64_t w) { return (w & kWordOwned) != 0; }
+__host__ __device__ inline bool word_flat(uint64_t w) { return (w & kWordFlat) != 0; }
 __host__ __device__ inline uint32_t word_next(uint64_t w) { return (uint32_t)w; }
 
 // Per-system control block: scheduling state and MINRES scalars.
@@ -58,7 +58,6 @@ struct alignas(64) Ctl {
   int zmode;                 // what the K_Z phase does (ZM_*)
   int pend;                  // 1: the previous step's update is deferred
   int fin_status, fin_iters; // finish after a ZM_FLUSH phase
-  int owned_ok;              // every workgroup of the solver's grid has started
 };
 
 // K_Z phase modes.  The w/x updates of MINRES run two steps at a time: a
@@ -127,6 +126,9 @@ struct SysDesc {
   double2 *Z[2];           // zhat_m = P^{-1} v_m / gamma_m, by parity of m
   double2 *W[2];           // search directions w_m, by parity of m
   double *part;            // per-tile partial sums
+  unsigned long long *slots;   // per-tile arrivals of a flat solve: two sets (by phase
+                               // parity) of kFlatSlots slots of two words
+  int flat;                // the system's own solves may run flat
   Ctl *ctl;
   DevInfo *info;
   // Lanczos coefficients of the last solve: lz[2 (j - 1)] = delta_j,
@@ -136,6 +138,10 @@ struct SysDesc {
 };
 
 constexpr int kLanczosCap = 4096;
+
+// Tiles of a phase of a flat solve, at most, and tiles a workgroup owns of one.
+constexpr int kFlatSlots = 1024;
+constexpr int kFlatOwn = 8;
 
 // Team phases: LDS of the line buffers (4096 FP64 points in up to 64 lines, and
 // one 16-byte element of padding a line) and of the workgroup (the twiddles of

@@ -248,7 +248,7 @@ __device__ __forceinline__ void tile_X(const SysDesc &S, const IOPtr &io, int it
     E::store_blk(o, t, [&](int, int, int q, Cx<double> v) { st_nt(out + q, v); });
   }
   const double s = wg_sum(acc, red);
-  if (threadIdx.x == 0) S.part[tile] = s;
+  if (threadIdx.x == 0) red[NT / 64] = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -261,7 +261,8 @@ __device__ __forceinline__ void tile_X(const SysDesc &S, const IOPtr &io, int it
 //     gamma_{j+1}^2 = <z_{j+1}, v_{j+1}> = <T', Tv_{j+1}> (W_c orthogonal).
 // ---------------------------------------------------------------------------
 template <typename R, int D, int LDSB, class E>
-__device__ __forceinline__ void tile_Y(const SysDesc &S, int kind, int iter, int tile, char *smem, double *red) {
+__device__ __forceinline__ void tile_Y(const SysDesc &S, const Ctl *C, int kind, int iter, int tile, char *smem,
+                                       double *red) {
   Cx<R> *buf = reinterpret_cast<Cx<R> *>(smem);
   const int ax = (kind == K_Y) ? 0 : 1;
   const R *Wm = E::matrix(S, ax);
@@ -279,7 +280,6 @@ __device__ __forceinline__ void tile_Y(const SysDesc &S, int kind, int iter, int
       const CSL_G double2 *__restrict__ v1 = gbl(S.Tv[1]);
       E::template fill<4>(buf, t, [&](int, int, int p) { return to_cx<R>(ldg(v1 + p)); });
     } else {
-      const Ctl *C = S.ctl;
       const double g = ld_ctl(&C->gamma), go = ld_ctl(&C->gamma_old);
       const double dl = ld_ctl(&C->delta);
       const double cd = dl / g, cg = g / go;
@@ -343,7 +343,7 @@ __device__ __forceinline__ void tile_Y(const SysDesc &S, int kind, int iter, int
   }
   if (kind == K_Y) {
     const double sg = wg_sum(gacc, red);
-    if (threadIdx.x == 0) S.part[tile] = sg;
+    if (threadIdx.x == 0) red[NT / 64] = sg;
   }
 }
 
@@ -354,11 +354,11 @@ __device__ __forceinline__ void tile_Y(const SysDesc &S, int kind, int iter, int
 // with x held as its conjugate (the user's z).
 // ---------------------------------------------------------------------------
 template <typename R, int D, int LDSB, class E>
-__device__ __forceinline__ void tile_Z(const SysDesc &S, const IOPtr &io, int iter, int tile, char *smem) {
+__device__ __forceinline__ void tile_Z(const SysDesc &S, const Ctl *C, const IOPtr &io, int iter, int tile,
+                                       char *smem) {
   const R *Wm = E::matrix(S, D - 1);
   Cx<R> *buf = reinterpret_cast<Cx<R> *>(smem);
   Cx<R> *twl = reinterpret_cast<Cx<R> *>(smem + LDSB);
-  const Ctl *C = S.ctl;
   const int j = iter;
   const int mode = j == 0 ? ZM_DEFER : ld_ctl(&C->zmode);
   CSL_G double2 *__restrict__ X = gbl(io.x);
@@ -511,7 +511,7 @@ __device__ __forceinline__ void tile_PR(const SysDesc &S, const IOPtr &io, int t
     acc += rx * rx + ry * ry;
   }
   const double s = wg_sum(acc, red);
-  if (threadIdx.x == 0) S.part[tile] = s;
+  if (threadIdx.x == 0) red[NT / 64] = s;
 }
 
 #if CSL_PLANE
@@ -808,7 +808,7 @@ __device__ __forceinline__ void tile_XW(const SysDesc &S, int iter, int tile, ch
     __syncthreads();
   }
   const double s = wg_sum(acc, red);
-  if (threadIdx.x == 0) S.part[tile] = s;
+  if (threadIdx.x == 0) red[NT / 64] = s;
 }
 
 // Phase Z of a plane solve with rows of n2 = N - 1 <= 127 points, per wave as
@@ -820,14 +820,14 @@ __device__ __forceinline__ void tile_XW(const SysDesc &S, int iter, int tile, ch
 // transform's rounding; the flush of a deferred step (no transform) is
 // tile_Z's.
 template <typename R, int LDSB>
-__device__ __forceinline__ void tile_ZW(const SysDesc &S, const IOPtr &io, int iter, int tile, char *smem) {
+__device__ __forceinline__ void tile_ZW(const SysDesc &S, const Ctl *C, const IOPtr &io, int iter, int tile,
+                                        char *smem) {
   constexpr int W = NT / 64;
   constexpr bool kHalf = sizeof(R) == 8;
-  const Ctl *C = S.ctl;
   const int j = iter;
   const int mode = j == 0 ? ZM_DEFER : ld_ctl(&C->zmode);
   if (mode == ZM_FLUSH) {
-    tile_Z<R, 3, LDSB, FftEng<R, LDSB>>(S, io, iter, tile, smem);
+    tile_Z<R, 3, LDSB, FftEng<R, LDSB>>(S, C, io, iter, tile, smem);
     return;
   }
   const int n2 = S.n[2], N = n2 + 1;
@@ -967,7 +967,7 @@ __device__ __forceinline__ void tile_ZW(const SysDesc &S, const IOPtr &io, int i
 // The plane tile: one part of one plane, in the preconditioner precision R
 // (FP32 in the 1024-thread instance, FP64 in the 512-thread one).
 template <typename R>
-__device__ __forceinline__ void tile_YP(const SysDesc &S, int iter, int tile, char *smem,
+__device__ __forceinline__ void tile_YP(const SysDesc &S, const Ctl *C, int iter, int tile, char *smem,
                                         double *red) {
   const int n0 = S.n[0], n1 = S.n[1];
   const int rows = S.rows;
@@ -997,7 +997,6 @@ __device__ __forceinline__ void tile_YP(const SysDesc &S, int iter, int tile, ch
   CSL_G double *__restrict__ vout = reinterpret_cast<CSL_G double *>(gbl(S.Tv[(j + 1) & 1])) + off;
   double cd = 0.0, cg = 0.0;
   if (j > 0) {
-    const Ctl *C = S.ctl;
     const double g = ld_ctl(&C->gamma), go = ld_ctl(&C->gamma_old);
     const double dl = ld_ctl(&C->delta);
     cd = dl / g;
@@ -1191,41 +1190,41 @@ __device__ __forceinline__ void tile_YP(const SysDesc &S, int iter, int tile, ch
   if constexpr (kHalf) plane_dst_pairs_half(pl, wbuf, tw1, n0, lg1, n1, 1, PlaneNoHook(), store);
   else plane_dst_pairs<R>(pl, wbuf, tw1, n0, lg1, n1, 1, PlaneNoHook(), store);
   const double sg = wg_sum(gacc, red);
-  if (threadIdx.x == 0) S.part[tile] = sg;
+  if (threadIdx.x == 0) red[NT / 64] = sg;
 }
 #endif  // CSL_PLANE
 
 #if CSL_TEAM
 template <int D>
-__device__ __forceinline__ void team_tile(const SysDesc &S, const IOPtr &io, int kind, int iter, int tile,
+__device__ __forceinline__ void team_tile(const SysDesc &S, const Ctl *C, const IOPtr &io, int kind, int iter, int tile,
                                           char *smem, double *red, double *carry) {
   if (kind == K_X) {
     tile_TX<D>(S, io, iter, tile, smem, red, carry);
   } else if (kind == K_Z) {
-    if (S.prec) tile_TZ<float, D>(S, io, iter, tile, smem, carry);
-    else tile_TZ<double, D>(S, io, iter, tile, smem, carry);
+    if (S.prec) tile_TZ<float, D>(S, C, io, iter, tile, smem, carry);
+    else tile_TZ<double, D>(S, C, io, iter, tile, smem, carry);
   } else if (kind == K_PR) {
     tile_PR<D>(S, io, tile, red);
   } else if (D == 3 && kind == K_Y) {
     if (S.prec) tile_TY0<float>(S, tile, smem, red, carry);
     else tile_TY0<double>(S, tile, smem, red, carry);
   } else {
-    if (S.prec) tile_TY<float, D>(S, kind, iter, tile, smem, red, carry);
-    else tile_TY<double, D>(S, kind, iter, tile, smem, red, carry);
+    if (S.prec) tile_TY<float, D>(S, C, kind, iter, tile, smem, red, carry);
+    else tile_TY<double, D>(S, C, kind, iter, tile, smem, red, carry);
   }
 }
 #endif
 
 template <int LDSB>
-__device__ __forceinline__ void process_tile(const SysDesc &S, const IOPtr &io, int kind, int iter, int tile,
-                             char *smem, double *red) {
+__device__ __forceinline__ void process_tile(const SysDesc &S, const Ctl *C, const IOPtr &io, int kind, int iter,
+                                             int tile, char *smem, double *red) {
 #if CSL_TEAM
   __shared__ double carry[2 * (NT / 64)];
 #if CSL_2D_FFT_ONLY
-  team_tile<2>(S, io, kind, iter, tile, smem, red, carry);
+  team_tile<2>(S, C, io, kind, iter, tile, smem, red, carry);
 #else
-  if (S.d == 3) team_tile<3>(S, io, kind, iter, tile, smem, red, carry);
-  else team_tile<2>(S, io, kind, iter, tile, smem, red, carry);
+  if (S.d == 3) team_tile<3>(S, C, io, kind, iter, tile, smem, red, carry);
+  else team_tile<2>(S, C, io, kind, iter, tile, smem, red, carry);
 #endif
   return;
 #else
@@ -1250,11 +1249,11 @@ __device__ __forceinline__ void process_tile(const SysDesc &S, const IOPtr &io, 
   if (g && S.gemm[ax] == 2 && S.prec && kind != K_X && kind != K_PR) {
     typedef GemmEng16<LDSB> G16;
     if (kind == K_Z) {
-      if (d3) tile_Z<float, 3, LDSB, G16>(S, io, iter, tile, smem);
-      else tile_Z<float, 2, LDSB, G16>(S, io, iter, tile, smem);
+      if (d3) tile_Z<float, 3, LDSB, G16>(S, C, io, iter, tile, smem);
+      else tile_Z<float, 2, LDSB, G16>(S, C, io, iter, tile, smem);
     } else {
-      if (d3) tile_Y<float, 3, LDSB, G16>(S, kind, iter, tile, smem, red);
-      else tile_Y<float, 2, LDSB, G16>(S, kind, iter, tile, smem, red);
+      if (d3) tile_Y<float, 3, LDSB, G16>(S, C, kind, iter, tile, smem, red);
+      else tile_Y<float, 2, LDSB, G16>(S, C, kind, iter, tile, smem, red);
     }
     return;
   }
@@ -1266,18 +1265,18 @@ __device__ __forceinline__ void process_tile(const SysDesc &S, const IOPtr &io, 
   }
   if (kind == K_Z && S.plane && S.lg[2] <= 8) {
 #if CSL_PLANE_F64
-    tile_ZW<double, LDSB>(S, io, iter, tile, smem);
+    tile_ZW<double, LDSB>(S, C, io, iter, tile, smem);
 #else
-    tile_ZW<float, LDSB>(S, io, iter, tile, smem);
+    tile_ZW<float, LDSB>(S, C, io, iter, tile, smem);
 #endif
     return;
   }
   if (kind == K_Y && S.plane) {
     // one precision per instance (the runtime launches the one of S.prec)
 #if CSL_PLANE_F64
-    tile_YP<double>(S, iter, tile, smem, red);
+    tile_YP<double>(S, C, iter, tile, smem, red);
 #else
-    tile_YP<float>(S, iter, tile, smem, red);
+    tile_YP<float>(S, C, iter, tile, smem, red);
 #endif
     return;
   }
@@ -1291,15 +1290,15 @@ __device__ __forceinline__ void process_tile(const SysDesc &S, const IOPtr &io, 
       break;
     case K_Z:
       if (S.prec) {
-        if (d3) g ? tile_Z<float, 3, LDSB, G32>(S, io, iter, tile, smem)
-                  : tile_Z<float, 3, LDSB, F32>(S, io, iter, tile, smem);
-        else g ? tile_Z<float, 2, LDSB, G32>(S, io, iter, tile, smem)
-               : tile_Z<float, 2, LDSB, F32>(S, io, iter, tile, smem);
+        if (d3) g ? tile_Z<float, 3, LDSB, G32>(S, C, io, iter, tile, smem)
+                  : tile_Z<float, 3, LDSB, F32>(S, C, io, iter, tile, smem);
+        else g ? tile_Z<float, 2, LDSB, G32>(S, C, io, iter, tile, smem)
+               : tile_Z<float, 2, LDSB, F32>(S, C, io, iter, tile, smem);
       } else {
-        if (d3) g ? tile_Z<double, 3, LDSB, G64>(S, io, iter, tile, smem)
-                  : tile_Z<double, 3, LDSB, F64>(S, io, iter, tile, smem);
-        else g ? tile_Z<double, 2, LDSB, G64>(S, io, iter, tile, smem)
-               : tile_Z<double, 2, LDSB, F64>(S, io, iter, tile, smem);
+        if (d3) g ? tile_Z<double, 3, LDSB, G64>(S, C, io, iter, tile, smem)
+                  : tile_Z<double, 3, LDSB, F64>(S, C, io, iter, tile, smem);
+        else g ? tile_Z<double, 2, LDSB, G64>(S, C, io, iter, tile, smem)
+               : tile_Z<double, 2, LDSB, F64>(S, C, io, iter, tile, smem);
       }
       break;
     case K_PR:
@@ -1308,15 +1307,15 @@ __device__ __forceinline__ void process_tile(const SysDesc &S, const IOPtr &io, 
       break;
     default:
       if (S.prec) {
-        if (d3) g ? tile_Y<float, 3, LDSB, G32>(S, kind, iter, tile, smem, red)
-                  : tile_Y<float, 3, LDSB, F32>(S, kind, iter, tile, smem, red);
-        else g ? tile_Y<float, 2, LDSB, G32>(S, kind, iter, tile, smem, red)
-               : tile_Y<float, 2, LDSB, F32>(S, kind, iter, tile, smem, red);
+        if (d3) g ? tile_Y<float, 3, LDSB, G32>(S, C, kind, iter, tile, smem, red)
+                  : tile_Y<float, 3, LDSB, F32>(S, C, kind, iter, tile, smem, red);
+        else g ? tile_Y<float, 2, LDSB, G32>(S, C, kind, iter, tile, smem, red)
+               : tile_Y<float, 2, LDSB, F32>(S, C, kind, iter, tile, smem, red);
       } else {
-        if (d3) g ? tile_Y<double, 3, LDSB, G64>(S, kind, iter, tile, smem, red)
-                  : tile_Y<double, 3, LDSB, F64>(S, kind, iter, tile, smem, red);
-        else g ? tile_Y<double, 2, LDSB, G64>(S, kind, iter, tile, smem, red)
-               : tile_Y<double, 2, LDSB, F64>(S, kind, iter, tile, smem, red);
+        if (d3) g ? tile_Y<double, 3, LDSB, G64>(S, C, kind, iter, tile, smem, red)
+                  : tile_Y<double, 3, LDSB, F64>(S, C, kind, iter, tile, smem, red);
+        else g ? tile_Y<double, 2, LDSB, G64>(S, C, kind, iter, tile, smem, red)
+               : tile_Y<double, 2, LDSB, F64>(S, C, kind, iter, tile, smem, red);
       }
       break;
   }
@@ -1395,35 +1394,25 @@ __device__ __forceinline__ void tile_pinv(const SysDesc &S, int pass, const doub
 // Givens recurrences, takes the stopping decision and publishes the next
 // phase of this system.
 // ---------------------------------------------------------------------------
-// The release exchange orders every earlier write of this thread (the reset
-// completion count, the scalars) before the new ticket word; on gfx950 an
-// agent-scope release writes back the L2, an acquire invalidates it, so no
-// fence beyond the one the protocol needs is issued.
-// Tiles of a phase that the workgroups of a single-system solve own from the
-// start (sg = the grid size; 0 for a batch or while some workgroup of the grid
-// has not started): each tile below min(sg, tiles) has one owner, which takes
-// it the first time it sees the phase, without a claim, and the claim counter
-// of the published phase starts after them.  Owners are used only once every
-// workgroup is resident, so that progress never waits on one that is not.
-__device__ __forceinline__ int static_tiles(const SysDesc &S, int kind, int sg) {
-  return kind < K_NKINDS ? min(sg, S.ntile[kind]) : 0;
-}
-
-// Owned tile of workgroup b in a grid of g: workgroups are dealt to the 8
+// Owned tiles of workgroup b in a grid of g: workgroups are dealt to the 8
 // XCDs round robin (b mod 8), and the workgroups of XCD x own tiles
-// [start_x, start_x + count_x) in order, a bijection of [0, g).  The
-// stencil's neighbouring rows then mostly come from tiles on the same XCD,
-// whose L2 already holds them.
+// [start_x, start_x + count_x) in order, a bijection of [0, g) (and the tiles g
+// further on of a phase with more).  The stencil's neighbouring rows then
+// mostly come from tiles on the same XCD, whose L2 already holds them.
 __device__ __forceinline__ int xcd_tile(int b, int g) {
   const int x = b & 7, i = b >> 3;
   const int q = g >> 3, r = g & 7;   // XCDs below r hold q + 1 workgroups
   return x * q + min(x, r) + i;
 }
 
-__device__ __forceinline__ void publish(const SysDesc &S, Ctl *C, int iter, int kind, int sg) {
+// The release exchange orders every earlier write of this thread (the reset
+// completion count, the scalars) before the new ticket word; on gfx950 an
+// agent-scope release writes back the L2, an acquire invalidates it, so no
+// fence beyond the one the protocol needs is issued.
+__device__ __forceinline__ void publish(const SysDesc &S, Ctl *C, int iter, int kind, bool flat) {
+  (void)S;
   __hip_atomic_store(&C->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int s0 = static_tiles(S, kind, sg);
-  const uint64_t w = make_word(iter, kind) + (s0 > 0 ? kWordOwned + (uint64_t)s0 : 0ull);
+  const uint64_t w = make_word(iter, kind) + (flat ? kWordFlat : 0ull);
   __hip_atomic_exchange(&C->word, (unsigned long long)w, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -1440,43 +1429,43 @@ __device__ __forceinline__ void finish(const SysDesc &S, Glob *G, int iter, int 
 
 enum { ST_OK = 0, ST_NOT_CONVERGED = 3, ST_BREAKDOWN = 4, ST_NONFINITE = 5 };
 
+// What follows a completed phase: the next one, or (kind K_DONE) the end of the
+// solve with its status, iterations and true residual.
+struct NextPhase {
+  int iter, kind;
+  int status, iters;
+  double rt;
+};
+
+__device__ __forceinline__ NextPhase next_phase(int iter, int kind) {
+  return NextPhase{iter, kind, 0, 0, 0.0};
+}
+__device__ __forceinline__ NextPhase next_done(int iter, int status, int iters, double rt) {
+  return NextPhase{iter, K_DONE, status, iters, rt};
+}
+
 // End a solve early at iteration iter with the iterate x_{iters}: if the
 // update of step iter - 1 is still deferred, run one K_Z phase that applies
-// it alone (ZM_FLUSH) and finish from its epilogue.
-__device__ __forceinline__ void end_solve(const SysDesc &S, Glob *G, Ctl *C, int iter, int status,
-                                          int iters, int sg) {
+// it alone (ZM_FLUSH) and finish after it.
+__device__ __forceinline__ NextPhase next_end(Ctl *C, int iter, int status, int iters) {
   if (C->pend) {
     C->pend = 0;
     C->zmode = ZM_FLUSH;
     C->fin_status = status;
     C->fin_iters = iters;
-    publish(S, C, iter, K_Z, sg);
-  } else {
-    finish(S, G, iter, status, iters, __longlong_as_double(0x7ff8000000000000ll));
+    return next_phase(iter, K_Z);
   }
+  return next_done(iter, status, iters, __longlong_as_double(0x7ff8000000000000ll));
 }
 
-__device__ __forceinline__ void epilogue(const SysDesc &S, const SolveParams &P, int kind, int iter, Glob *G,
-                         double *red, int sg) {
-  const int nt = S.ntile[kind];
-  const bool last_strided = (kind == K_Y);   // carries the gamma^2 partials
-  const bool need_sum = (kind == K_X) || (kind == K_PR) || last_strided;
-  double a = 0.0;
-  if (need_sum) {
-    for (int i = threadIdx.x; i < nt; i += NT) a += S.part[i];
-  }
-  const double sum = need_sum ? wg_sum(a, red) : 0.0;
-  if (threadIdx.x != 0) return;
-  Ctl *C = S.ctl;
+// One thread's step from the completed phase (kind, iter), whose tile partials
+// add up to sum, to what follows: the Lanczos and Givens recurrences on the
+// control block C and the stopping decision.  In a flat solve every workgroup
+// takes it on a copy of its own; the records of the solve (residual estimate,
+// Lanczos coefficients) are written by one of them (lead).
+__device__ __forceinline__ NextPhase advance(const SysDesc &S, const SolveParams &P, Ctl *C, bool lead,
+                                             int kind, int iter, double sum) {
   const double nan = __longlong_as_double(0x7ff8000000000000ll);
-  // owners for the phases published here only once every workgroup has
-  // started (recorded in the control block, so the count is read until then)
-  if (sg > 0 && !C->owned_ok) {
-    if (__hip_atomic_load(&G->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= sg)
-      C->owned_ok = 1;
-    else
-      sg = 0;
-  }
   const bool five = (S.d == 3) && !S.plane;   // 3-D with the three strided phases
   const int first_strided = five ? K_Y1 : K_Y;
   if (kind == K_X) {
@@ -1484,43 +1473,32 @@ __device__ __forceinline__ void epilogue(const SysDesc &S, const SolveParams &P,
       const double bn = sqrt(sum);
       C->bnorm = bn;
       if (!isfinite(bn)) {
-        S.info->relres_est = nan;
-        finish(S, G, iter, ST_NONFINITE, 0, nan);
-      } else if (bn == 0.0) {
-        S.info->relres_est = 0.0;
-        finish(S, G, iter, ST_OK, 0, 0.0);
-      } else {
-        publish(S, C, 0, first_strided, sg);
+        if (lead) S.info->relres_est = nan;
+        return next_done(iter, ST_NONFINITE, 0, nan);
       }
-    } else if (!isfinite(sum)) {
-      end_solve(S, G, C, iter, ST_NONFINITE, iter - 1, sg);
-    } else {
-      C->delta = sum;
-      publish(S, C, iter, first_strided, sg);
+      if (bn == 0.0) {
+        if (lead) S.info->relres_est = 0.0;
+        return next_done(iter, ST_OK, 0, 0.0);
+      }
+      return next_phase(0, first_strided);
     }
-    return;
+    if (!isfinite(sum)) return next_end(C, iter, ST_NONFINITE, iter - 1);
+    C->delta = sum;
+    return next_phase(iter, first_strided);
   }
-  if (kind == K_Y1) {
-    publish(S, C, iter, K_Y, sg);
-    return;
-  }
-  if (kind == K_Y1I) {
-    publish(S, C, iter, K_Z, sg);
-    return;
-  }
-  if (last_strided) {
+  if (kind == K_Y1) return next_phase(iter, K_Y);
+  if (kind == K_Y1I) return next_phase(iter, K_Z);
+  if (kind == K_Y) {   // the last strided phase with a sum: the gamma^2 partials
     const double g2 = sum;
     if (!isfinite(g2)) {
-      S.info->relres_est = nan;
-      if (iter == 0) finish(S, G, iter, ST_NONFINITE, 0, nan);
-      else end_solve(S, G, C, iter, ST_NONFINITE, iter - 1, sg);
-      return;
+      if (lead) S.info->relres_est = nan;
+      if (iter == 0) return next_done(iter, ST_NONFINITE, 0, nan);
+      return next_end(C, iter, ST_NONFINITE, iter - 1);
     }
     if (iter == 0) {
       if (g2 <= 0.0) {
-        S.info->relres_est = nan;
-        finish(S, G, iter, ST_BREAKDOWN, 0, nan);
-        return;
+        if (lead) S.info->relres_est = nan;
+        return next_done(iter, ST_BREAKDOWN, 0, nan);
       }
       const double g = sqrt(g2);
       C->gamma = g;
@@ -1533,17 +1511,13 @@ __device__ __forceinline__ void epilogue(const SysDesc &S, const SolveParams &P,
       C->s_old = 0.0;
       C->after_z = 0;
       C->pend = 0;
-      publish(S, C, 0, five ? K_Y1I : K_Z, sg);
-      return;
+      return next_phase(0, five ? K_Y1I : K_Z);
     }
-    if (g2 < 0.0) {
-      end_solve(S, G, C, iter, ST_BREAKDOWN, iter - 1, sg);
-      return;
-    }
+    if (g2 < 0.0) return next_end(C, iter, ST_BREAKDOWN, iter - 1);
     // Givens rotations of column j of the Lanczos tridiagonal (step j)
     const double gn = sqrt(g2);
     const double dl = C->delta, g = C->gamma;
-    if (iter <= kLanczosCap) {
+    if (lead && iter <= kLanczosCap) {
       S.lz[2 * (iter - 1)] = dl;
       S.lz[2 * (iter - 1) + 1] = gn;
       S.lz[2 * kLanczosCap] = (double)iter;
@@ -1565,7 +1539,8 @@ __device__ __forceinline__ void epilogue(const SysDesc &S, const SolveParams &P,
     C->e2 = e2;
     C->e3 = e3;
     C->ceta = cn * eta;
-    C->eta = -sn * eta;
+    const double etan = -sn * eta;
+    C->eta = etan;
     C->c_old = c;
     C->c = cn;
     C->s_old = s;
@@ -1573,53 +1548,155 @@ __device__ __forceinline__ void epilogue(const SysDesc &S, const SolveParams &P,
     C->gamma_old = g;
     C->gamma = gn;
     // decide what follows the update of x_j (phase K_Z)
-    const double est = fabs(C->eta) / C->eta0;
-    S.info->relres_est = est;
+    const double est = fabs(etan) / C->eta0;
+    if (lead) S.info->relres_est = est;
+    int after = 0;
     if (gn == 0.0) {
-      C->after_z = 2;
+      after = 2;
       C->finishing = ST_OK;
     } else if (est <= P.tol) {
-      C->after_z = P.check_true ? 1 : 2;
+      after = P.check_true ? 1 : 2;
       C->finishing = P.check_true ? -1 : ST_OK;
     } else if (iter >= P.maxit) {
-      C->after_z = 2;
+      after = 2;
       C->finishing = ST_NOT_CONVERGED;
-    } else {
-      C->after_z = 0;
     }
-    const int zm = C->pend ? ZM_PAIR : (C->after_z != 0 ? ZM_SINGLE : ZM_DEFER);
+    C->after_z = after;
+    const int zm = C->pend ? ZM_PAIR : (after != 0 ? ZM_SINGLE : ZM_DEFER);
     C->zmode = zm;
     C->pend = (zm == ZM_DEFER);
-    publish(S, C, iter, five ? K_Y1I : K_Z, sg);
-    return;
+    return next_phase(iter, five ? K_Y1I : K_Z);
   }
   if (kind == K_Z) {
-    if (iter > 0 && C->zmode == ZM_FLUSH) finish(S, G, iter, C->fin_status, C->fin_iters, nan);
-    else if (iter == 0 || C->after_z == 0) publish(S, C, iter + 1, K_X, sg);
-    else publish(S, C, iter, K_PR, sg);
-    return;
+    if (iter > 0 && C->zmode == ZM_FLUSH) return next_done(iter, C->fin_status, C->fin_iters, nan);
+    if (iter == 0 || C->after_z == 0) return next_phase(iter + 1, K_X);
+    return next_phase(iter, K_PR);
   }
-  if (kind == K_PR) {
-    const int k = iter;
-    const double rt = sqrt(sum) / C->bnorm;
-    if (C->finishing >= 0) {
-      finish(S, G, iter, C->finishing, k, rt);
-    } else if (rt <= P.tol) {
-      finish(S, G, iter, ST_OK, k, rt);
-    } else if (k >= P.maxit) {
-      finish(S, G, iter, ST_NOT_CONVERGED, k, rt);
-    } else {
-      publish(S, C, iter + 1, K_X, sg);
+  // K_PR
+  const double rt = sqrt(sum) / C->bnorm;
+  if (C->finishing >= 0) return next_done(iter, C->finishing, iter, rt);
+  if (rt <= P.tol) return next_done(iter, ST_OK, iter, rt);
+  if (iter >= P.maxit) return next_done(iter, ST_NOT_CONVERGED, iter, rt);
+  return next_phase(iter + 1, K_X);
+}
+
+// The phases whose tiles carry a partial sum.
+__device__ __forceinline__ bool has_partial(int kind) { return kind == K_X || kind == K_Y || kind == K_PR; }
+
+// Phase epilogue, run by the workgroup that completed the last tile of a
+// phase: sums the tile partials in a fixed order, takes the step to the next
+// phase and publishes it.  sg: the grid of a single-system solve that may run
+// flat, 0 otherwise; once every workgroup of it has started, the next phase is
+// published flat.
+__device__ __forceinline__ void epilogue(const SysDesc &S, const SolveParams &P, int kind, int iter, Glob *G,
+                         double *red, int sg) {
+  const int nt = S.ntile[kind];
+  const bool need_sum = has_partial(kind);
+  double a = 0.0;
+  if (need_sum) {
+    for (int i = threadIdx.x; i < nt; i += NT) a += S.part[i];
+  }
+  const double sum = need_sum ? wg_sum(a, red) : 0.0;
+  if (threadIdx.x != 0) return;
+  const bool flat =
+      sg > 0 && __hip_atomic_load(&G->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= sg;
+  const NextPhase n = advance(S, P, S.ctl, true, kind, iter, sum);
+  if (n.kind == K_DONE) finish(S, G, n.iter, n.status, n.iters, n.rt);
+  else publish(S, S.ctl, n.iter, n.kind, flat);
+}
+
+// ---------------------------------------------------------------------------
+// Flat solve: a single system whose workgroups have all started goes on without
+// claims, completion counts and published phases.  Workgroup b owns tiles
+// xcd_tile(b), xcd_tile(b) + grid, .. of every phase.  Having finished them it
+// releases its writes and marks the tiles' slots with the phase number and
+// their partial sums; then it waits for the slots of all tiles of the phase,
+// adds up the partials and takes the step to the next phase on its own copy of
+// the control block (all copies are the same: the sums are in the order of the
+// claimed phases).  One write and one read of the slots replace the hand-off
+// by one counter (a few hundred atomic increments of one word, some 50 ns
+// each), an epilogue in one workgroup and the published word: 15 us a phase on
+// 256 workgroups before (511^2, FP64).
+// A slot is two words, each half a partial beside the 32-bit phase number, so
+// a word is valid by itself; two sets of slots alternate, because a workgroup
+// may mark the next phase while another still reads this one (it cannot get
+// two ahead: that needs the other's mark of the next).
+// Every workgroup of the grid is resident here (it has been counted), so the
+// wait ends; the time limit bounds it as well: past it a workgroup raises
+// G->error, and those that wait for it leave too.
+// ---------------------------------------------------------------------------
+__shared__ Ctl s_ctl;
+
+// End of the workgroup's part of a phase (its no owned tiles done, their
+// partials in own_part): returns the next phase's kind, its iteration in
+// sh_iter, or -1 when the solve is over.
+__device__ __forceinline__ int flat_phase_end(const SysDesc &S, const SolveParams &P, Glob *G, int kind,
+                                              int iter, int no, const double *own_part, unsigned seq,
+                                              long long t0, double *red, int *sh_next) {
+  const int tid = threadIdx.x, nt = S.ntile[kind];
+  const int sg = (int)gridDim.x, own = xcd_tile((int)blockIdx.x, sg);
+  unsigned long long *slots = S.slots + (size_t)(seq & 1) * 2 * kFlatSlots;
+  if (tid == 0) {
+    sh_next[2] = 0;
+    if (no > 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      for (int i = 0; i < no; ++i) {
+        const unsigned long long v = (unsigned long long)__double_as_longlong(own_part[i]);
+        unsigned long long *w = slots + 2 * (own + i * sg);
+        const unsigned long long mark = (unsigned long long)seq << 32;
+        __hip_atomic_store(w, mark | (v >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(w + 1, mark | (v & 0xffffffffull), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      }
     }
-    return;
   }
+  __syncthreads();
+  double a = 0.0;
+  for (int i = tid; i < nt; i += NT) {
+    unsigned long long hi, lo;
+    for (int spin = 0;; ++spin) {
+      hi = __hip_atomic_load(slots + 2 * i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      lo = __hip_atomic_load(slots + 2 * i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((unsigned)(hi >> 32) == seq && (unsigned)(lo >> 32) == seq) break;
+      __builtin_amdgcn_s_sleep(1);
+      if ((spin & 63) == 63 &&
+          (__hip_atomic_load(&G->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
+           wall_clock64() - t0 > P.timeout_ticks)) {
+        sh_next[2] = 1;
+        break;
+      }
+    }
+    a += __longlong_as_double((long long)((hi << 32) | (lo & 0xffffffffull)));
+  }
+  const double sum = wg_sum(a, red);
+  if (tid == 0) {
+    // the other workgroups' writes of this phase, for the whole workgroup
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    int nk = -1;
+    if (sh_next[2] == 0 && wall_clock64() - t0 <= P.timeout_ticks) {
+      const bool lead = blockIdx.x == 0;
+      const NextPhase n = advance(S, P, &s_ctl, lead, kind, iter, has_partial(kind) ? sum : 0.0);
+      if (n.kind != K_DONE) {
+        nk = n.kind;
+        sh_next[1] = n.iter;
+      } else if (lead) {
+        finish(S, G, n.iter, n.status, n.iters, n.rt);
+      }
+    } else {
+      __hip_atomic_fetch_or(&G->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    sh_next[0] = nk;
+  }
+  __syncthreads();
+  return sh_next[0];
 }
 
 // ---------------------------------------------------------------------------
 // Persistent solver: every workgroup repeatedly claims a tile of whichever
 // system has one ready, processes it, and the workgroup that completes a
 // phase runs its epilogue.  A workgroup never waits while holding a tile,
-// so progress does not depend on which workgroups are resident.  Idle
+// so progress does not depend on which workgroups are resident (a single
+// system goes over to the flat solve once all of them are).  Idle
 // workgroups exit when every system is done or the time limit passes; past
 // the limit no phase is published any more, so a system stops where it is
 // (status left unset) instead of running on in the workgroups still busy.
@@ -1629,8 +1706,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
     const SysDesc *__restrict__ sys, const IOPtr *__restrict__ io, IOPtr io0, int nsys,
     SolveParams P, Glob *G) {
   extern __shared__ __align__(16) char smem[];
-  __shared__ double red[NT / 64];
-  __shared__ int sh_s, sh_tile, sh_kind, sh_iter, sh_last;
+  __shared__ double red[NT / 64 + 1];   // wave sums, then the tile's partial
+  __shared__ int sh_s, sh_tile, sh_kind, sh_iter, sh_last, sh_next[3];
+  __shared__ double own_part[kFlatOwn];
   const int tid = threadIdx.x;
 #if CSL_TEAM
   team_stage_twiddles(smem);
@@ -1645,47 +1723,47 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
   // the next phase soonest; a batch keeps workgroups busy with other
   // systems, and polls less (about 14 us).
   const int bcap = nsys > 1 ? 64 : 1;
-  // a single system: once every workgroup has started, phases are published
-  // with tiles 0 .. min(grid, tiles) - 1 owned by workgroups, one each
-  // (xcd_tile)
-  const int sg = nsys == 1 ? (int)gridDim.x : 0;
+  // a single system: once every workgroup has started, the next phase is
+  // published flat, and every workgroup that sees it goes on flat
+  const int sg = nsys == 1 && sys[0].flat ? (int)gridDim.x : 0;
   if (tid == 0) __hip_atomic_fetch_add(&G->arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  unsigned seen = 0xffffffffu;   // [iter | kind] of the last owned tile taken
+  // flat solve: the phase, the next tile this workgroup owns of it, the tiles
+  // it has done
+  bool flat = false;
+  int fkind = 0, fiter = 0, ftile = 0, fdone = 0;
+  unsigned fseq = 0;
   for (;;) {
-    if (tid < 64) {
+    if (flat && ftile >= sys[0].ntile[fkind]) {
+      fkind = flat_phase_end(sys[0], P, G, fkind, fiter, fdone, own_part, ++fseq, t0, red, sh_next);
+      if (fkind < 0) break;
+      fiter = sh_next[1];
+      ftile = xcd_tile((int)blockIdx.x, sg);
+      fdone = 0;
+      continue;
+    }
+    if (!flat && tid < 64) {
       const int lane = tid;
       int found = -1;
       if (sg > 0) {
-        // single system: the workgroup's own tile of a phase it has not
-        // served yet, else a tile past the owned ones from the counter
         if (lane == 0) {
           const uint64_t w = __hip_atomic_load(&sys[0].ctl->word, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
           const int kd = word_kind(w);
-          if (kd < K_NKINDS) {
-            const int it = word_iter(w);
-            const unsigned key = (unsigned)(w >> 32);
-            // workgroup b (on XCD b mod 8) owns tile xcd_tile(b): each XCD a
-            // contiguous run of tiles, so neighbouring tiles share an L2
-            const int own = xcd_tile((int)blockIdx.x, sg);
-            if (word_owned(w) && key != seen && own < static_tiles(sys[0], kd, sg)) {
-              seen = key;
-              sh_tile = own;
-              sh_kind = kd;
-              sh_iter = it;
+          if (word_flat(w)) {
+            sh_kind = kd;
+            sh_iter = word_iter(w);
+            found = -3;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+          } else if (kd < K_NKINDS && word_next(w) < (uint32_t)sys[0].ntile[kd]) {
+            const uint64_t w2 = __hip_atomic_fetch_add(&sys[0].ctl->word, 1ull, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT);
+            const int kd2 = word_kind(w2);
+            if (!word_flat(w2) && kd2 < K_NKINDS && word_next(w2) < (uint32_t)sys[0].ntile[kd2]) {
+              sh_tile = (int)word_next(w2);
+              sh_kind = kd2;
+              sh_iter = word_iter(w2);
               found = 0;
               __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            } else if (word_next(w) < (uint32_t)sys[0].ntile[kd]) {
-              const uint64_t w2 = __hip_atomic_fetch_add(&sys[0].ctl->word, 1ull, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT);
-              const int kd2 = word_kind(w2);
-              if (kd2 < K_NKINDS && word_next(w2) < (uint32_t)sys[0].ntile[kd2]) {
-                sh_tile = (int)word_next(w2);
-                sh_kind = kd2;
-                sh_iter = word_iter(w2);
-                found = 0;
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-              }
             }
           }
         }
@@ -1735,7 +1813,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
       if (found >= 0) {
         cur = found;
         backoff = 0;
-      } else {
+      } else if (found == -1) {
         // nothing ready: stop when every system is done or on error / time
         // limit, else back off exponentially (up to bcap rounds) before looking again
         if (__hip_atomic_load(&G->active, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= 0 ||
@@ -1752,19 +1830,40 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
       }
       if (lane == 0) sh_s = found;
     }
-    __syncthreads();
-    const int s = sh_s;
+    if (!flat) {
+      __syncthreads();
+      if (sh_s == -3) {   // from here on flat; the acquire was taken above
+        if (tid == 0) s_ctl = *sys[0].ctl;
+        flat = true;
+        fkind = sh_kind;
+        fiter = sh_iter;
+        ftile = xcd_tile((int)blockIdx.x, sg);
+        __syncthreads();
+        continue;
+      }
+    }
+    const int s = flat ? 0 : sh_s;
     if (s == -2) break;
     if (s >= 0) {
-      const int kind = sh_kind, iter = sh_iter, tile = sh_tile;
+      const int kind = flat ? fkind : sh_kind, iter = flat ? fiter : sh_iter;
+      const int tile = flat ? ftile : sh_tile;
       const SysDesc &S = sys[s];
       const IOPtr iop = io ? io[s] : io0;
-      process_tile<LDSB>(S, iop, kind, iter, tile, smem, red);
+      process_tile<LDSB>(S, flat ? &s_ctl : S.ctl, iop, kind, iter, tile, smem, red);
+      if (flat) {
+        if (tid == 0) own_part[fdone] = red[NT / 64];
+        ++fdone;
+        ftile += sg;
+        // every wave's stores are complete at the barrier
+        __syncthreads();
+        continue;
+      }
       // every wave's stores are complete at the barrier; one agent-scope
       // release fence then publishes them with the (relaxed) completion
       // count, and only the workgroup that completes the phase acquires
       __syncthreads();
       if (tid == 0) {
+        S.part[tile] = red[NT / 64];
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         const unsigned old = __hip_atomic_fetch_add(&S.ctl->done, 1u, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);
@@ -1789,6 +1888,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
 
 #if !CSL_SOLVE_ONLY
 __global__ void init_kernel(const SysDesc *__restrict__ sys, int nsys, Glob *G) {
+  if (nsys == 1 && sys[0].flat) {
+    for (int i = threadIdx.x; i < 4 * kFlatSlots; i += blockDim.x) sys[0].slots[i] = 0;
+  }
   for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
     Ctl *C = sys[s].ctl;
     C->word = make_word(0, K_X);
@@ -1797,7 +1899,6 @@ __global__ void init_kernel(const SysDesc *__restrict__ sys, int nsys, Glob *G) 
     C->after_z = 0;
     C->pend = 0;
     C->zmode = ZM_DEFER;
-    C->owned_ok = 0;
     DevInfo *I = sys[s].info;
     I->status = -1;
     I->iters = 0;
@@ -2311,7 +2412,7 @@ hipError_t solve_occupancy(size_t smem, int *blocks_per_cu) {
 
 #if !CSL_SOLVE_ONLY
 hipError_t launch_init(const SysDesc *dsys, int nsys, Glob *G, hipStream_t s) {
-  hipLaunchKernelGGL(init_kernel, dim3(1), dim3(64), 0, s, dsys, nsys, G);
+  hipLaunchKernelGGL(init_kernel, dim3(1), dim3(256), 0, s, dsys, nsys, G);
   return hipGetLastError();
 }
 

@@ -573,6 +573,12 @@ hipError_t launch_pinv_all(csl_problem p, const double2 *x, double2 *y, hipStrea
   return hipSuccess;
 }
 
+// A solve of at most mt tiles a phase on `grid` workgroups may run flat (see the
+// solver's flat solve): every tile has a slot, a workgroup owns a few tiles of a phase.
+int flat_ok(int mt, int grid) {
+  return mt <= kFlatSlots && mt <= kFlatOwn * std::max(1, grid) ? 1 : 0;
+}
+
 // Schedule of a problem's own solves: the creation-time tiling with an LDS
 // budget of at least `lds_bytes` and chunks grouped into tiles of
 // `tile_points` points (0: about one tile per workgroup and phase, since a
@@ -608,6 +614,7 @@ csl_status configure_single(csl_problem p, int tile_points, int lds_bytes, int b
   set_tile_points(h, tp);
   int mt = 1;
   for (int k = 0; k < K_NKINDS; ++k) mt = std::max(mt, h.ntile[k]);
+  h.flat = flat_ok(mt, std::min(mt, cap));
   HIPCHK(hipMemcpyAsync(p->d_desc, &h, sizeof(SysDesc), hipMemcpyHostToDevice, s));
   HIPCHK(hipMemcpyAsync(p->d_desc0, &p->h0, sizeof(SysDesc), hipMemcpyHostToDevice, s));
   HIPCHK(hipStreamSynchronize(s));
@@ -931,6 +938,7 @@ static csl_status create_problem_impl(const csl_grid *grid, const double *a_noda
     part_cap = std::max(part_cap, t.maxtile);
   }
   const size_t o_part = take(sizeof(double) * std::max(part_cap, team_max_tiles(h)));
+  const size_t o_slots = take(sizeof(unsigned long long) * 4 * kFlatSlots);
   const size_t o_ctl = take(sizeof(Ctl));
   const size_t o_info = take(sizeof(DevInfo));
   const size_t o_glob = take(sizeof(Glob));
@@ -974,6 +982,7 @@ static csl_status create_problem_impl(const csl_grid *grid, const double *a_noda
   h.W[1] = (double2 *)(base + o_v[6]);
   h.T = base + o_t;
   h.part = (double *)(base + o_part);
+  h.slots = (unsigned long long *)(base + o_slots);
   h.ctl = (Ctl *)(base + o_ctl);
   h.info = (DevInfo *)(base + o_info);
   p->glob = (Glob *)(base + o_glob);
@@ -1336,6 +1345,7 @@ csl_status minres_solve_noalloc(const csl_grid *grid, const double *a_nodal, dou
   const size_t o_stats = take(sizeof(double) * 4);
   const size_t o_spart = take(sizeof(double) * 4 * stats_nblk);
   const size_t o_part = take(sizeof(double) * std::max(h.maxtile, team_max_tiles(h)));
+  const size_t o_slots = take(sizeof(unsigned long long) * 4 * kFlatSlots);
   const size_t o_lz = take(sizeof(double) * (2 * kLanczosCap + 1));
   const size_t o_mu = take(sizeof(double) * nmu);
   const size_t o_muf = take(sizeof(float) * nmu);
@@ -1381,6 +1391,7 @@ csl_status minres_solve_noalloc(const csl_grid *grid, const double *a_nodal, dou
   h.ctl = (Ctl *)(base + o_ctl);
   h.info = (DevInfo *)(base + o_info);
   h.part = (double *)(base + o_part);
+  h.slots = (unsigned long long *)(base + o_slots);
   h.lz = (double *)(base + o_lz);
   h.Tq = (double2 *)(base + o_v[0]);
   h.Tv[0] = (double2 *)(base + o_v[1]);
@@ -1438,6 +1449,7 @@ csl_status minres_solve_noalloc(const csl_grid *grid, const double *a_nodal, dou
   set_tile_points(h, (int)std::min<long long>(1 << 30, h.M / cap));
   int mt = 1;
   for (int k = 0; k < K_NKINDS; ++k) mt = std::max(mt, h.ntile[k]);
+  h.flat = flat_ok(mt, std::min(mt, cap));
   HIPCHK(wg256::launch_write_desc(h, d_desc, s));
   const SolveParams P = make_params(so.tol, so.maxit, so.check_true_residual, so.timeout_ms,
                                     sd.wall_khz);

@@ -527,7 +527,7 @@ __device__ __forceinline__ void tile_TX(const SysDesc &S, const IOPtr &io, int i
     __syncthreads();
   }
   const double s = wg_sum(acc, red);
-  if (threadIdx.x == 0) S.part[tile] = s;
+  if (threadIdx.x == 0) red[NT / 64] = s;
 }
 
 // Factor of P^{-1} for the mode with the eigenvalue sum lam.
@@ -577,7 +577,7 @@ __device__ __forceinline__ double team_scale(const SysDesc &S, Cx<R> *lb, Team &
 // No workgroup barrier for lines of at most 511 points.
 // ---------------------------------------------------------------------------
 template <typename R, int D>
-__device__ __forceinline__ void tile_TY(const SysDesc &S, int kind, int iter, int tile, char *smem,
+__device__ __forceinline__ void tile_TY(const SysDesc &S, const Ctl *C, int kind, int iter, int tile, char *smem,
                                         double *red, double *carry) {
   constexpr int ax = D - 2;
   Team t = make_team<R>(S.n[ax]);
@@ -597,7 +597,6 @@ __device__ __forceinline__ void tile_TY(const SysDesc &S, int kind, int iter, in
   const CSL_G double2 *vm = iter >= 2 ? vout : tq;
   double cd = 0.0, cg = 0.0;
   if (first && iter > 0) {
-    const Ctl *C = S.ctl;
     const double g = ld_ctl(&C->gamma), go = ld_ctl(&C->gamma_old);
     cd = ld_ctl(&C->delta) / g;
     cg = iter >= 2 ? g / go : 0.0;
@@ -667,7 +666,7 @@ __device__ __forceinline__ void tile_TY(const SysDesc &S, int kind, int iter, in
   }
   if (kind == K_Y) {
     const double sg = wg_sum(gacc, red);
-    if (threadIdx.x == 0) S.part[tile] = sg;
+    if (threadIdx.x == 0) red[NT / 64] = sg;
   }
 }
 
@@ -728,7 +727,7 @@ __device__ __forceinline__ void tile_TY0(const SysDesc &S, int tile, char *smem,
     __syncthreads();
   }
   const double sg = wg_sum(gacc, red);
-  if (threadIdx.x == 0) S.part[tile] = sg;
+  if (threadIdx.x == 0) red[NT / 64] = sg;
 }
 
 // ---------------------------------------------------------------------------
@@ -737,8 +736,8 @@ __device__ __forceinline__ void tile_TY0(const SysDesc &S, int tile, char *smem,
 // team transforms its row and applies the step's update to its points.
 // ---------------------------------------------------------------------------
 template <typename R, int D>
-__device__ __forceinline__ void tile_TZ(const SysDesc &S, const IOPtr &io, int iter, int tile, char *smem,
-                                        double *carry) {
+__device__ __forceinline__ void tile_TZ(const SysDesc &S, const Ctl *C, const IOPtr &io, int iter, int tile,
+                                        char *smem, double *carry) {
   Team t = make_team<R>(S.n[D - 1]);
   const int G = S.lpt_z, lgG = ilog2i(G);
   Cx<R> *buf = reinterpret_cast<Cx<R> *>(smem);
@@ -746,7 +745,6 @@ __device__ __forceinline__ void tile_TZ(const SysDesc &S, const IOPtr &io, int i
   Cx<R> *lb = buf + t.g * t.LS;
   const int r0 = tile * S.cpt[K_Z] * G, r1 = min(S.rows, (tile + 1) * S.cpt[K_Z] * G);
   const int ld = S.ld, n = t.n, j = iter;
-  const Ctl *C = S.ctl;
   const int mode = j == 0 ? ZM_DEFER : ld_ctl(&C->zmode);
   CSL_G double2 *X = gbl(io.x);
   CSL_G double2 *znew = gbl(S.Z[(j + 1) & 1]);
