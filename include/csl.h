@@ -288,7 +288,7 @@ typedef struct csl_batch_opts {
     int use_graph;          /* 1: replay a captured hipGraph per solve          */
     int tile_points;        /* grid points per scheduling tile (0 = by the
                                batch: about one tile per workgroup and phase,
-                               4096 to 16384, for 2-D FFT systems, else 8192);
+                               4096 to 20480, on 512 threads, else 8192);
                                larger tiles mean fewer cross-workgroup
                                hand-offs, smaller ones more parallelism    */
     int lds_bytes;          /* LDS line budget per workgroup: 0 = per

@@ -196,8 +196,10 @@ void plane_tiling(SysDesc &h) {
 // every axis): a round holds one line per team, a chunk is a round.  te > 0:
 // rounds of te FFT elements, as the other tilings take it.  target > 0: rounds
 // of fewer lines while that gives at most `target` of them (a solve that has
-// the device to itself spreads its lines over the CUs), down to one line per
-// wave.
+// the device to itself spreads its lines over the CUs), down to one wave's
+// lines and four: the row phases then still move 64-byte runs, and more
+// workgroups meet more slowly than they work (511^2 FP64 1.96 ms with four
+// lines, 2.22 with two, 2.5 with eight; 255^2 1.46 and 1.62 ms with four and two).
 void team_tiling(SysDesc &h, int te, int target) {
   auto round_lines = [&](int n, long long lines) {
     int g = team_lines(n);
@@ -206,7 +208,7 @@ void team_tiling(SysDesc &h, int te, int target) {
       while (want * 2 <= te / (2 * (n + 1))) want *= 2;
       return std::min(g, want);
     }
-    const int lo = std::max(1, 64 / team_lanes(n));
+    const int lo = std::max(4, 64 / team_lanes(n));
     while (g > lo && (lines + g / 2 - 1) / (g / 2) <= target) g /= 2;
     return g;
   };
@@ -432,6 +434,16 @@ void choose_tiles(SysDesc &h, int tile_elems, int ldsb_min, size_t *smem_out) {
   *smem_out = (smem <= 32768 && Lmax <= 1024 && ldsb == 32768) ? smem : 65536;
 }
 
+// Tiles of cpts[k] chunks.
+static void set_chunks_per_tile(SysDesc &h, const int (&cpts)[K_NKINDS]) {
+  // ntile <= nchunk, so the partials buffer sized by the chunk counts (maxtile)
+  // holds every tile's partial
+  for (int k = 0; k < K_NKINDS; ++k) {
+    h.cpt[k] = (h.plane && k == K_Y) ? 1 : cpts[k];   // one part of one plane per tile
+    h.ntile[k] = h.nchunk[k] > 0 ? (h.nchunk[k] + h.cpt[k] - 1) / h.cpt[k] : 0;
+  }
+}
+
 // Group chunks into tiles of about `points` grid points each (1 chunk per
 // tile when points <= 0): fewer, larger tiles mean fewer cross-workgroup
 // hand-offs (each one an L2 write-back and invalidate) per phase.
@@ -447,13 +459,17 @@ void set_tile_points(SysDesc &h, int points) {
     if (h.d == 3) cpts[K_Y1] = cpts[K_Y1I] = per(h.lpt_s[1] * h.n[1]);
     cpts[K_PR] = per(h.rpt * nlast);
   }
-  if (h.plane) cpts[K_Y] = 1;   // one part of one plane (held in LDS) per tile
-  // ntile <= nchunk, so the partials buffer sized by the chunk counts (maxtile)
-  // holds every tile's partial
-  for (int k = 0; k < K_NKINDS; ++k) {
-    h.cpt[k] = cpts[k];
-    h.ntile[k] = h.nchunk[k] > 0 ? (h.nchunk[k] + cpts[k] - 1) / cpts[k] : 0;
-  }
+  set_chunks_per_tile(h, cpts);
+}
+
+// At most one tile per workgroup and phase, for a solve that has the device to
+// itself: a phase of a few tiles more than workgroups takes twice as long as
+// one of a few less (255^3 FP64 on 512 workgroups: 581 tiles a phase 106 ms,
+// 452 or fewer 76 ms).
+void set_tiles_per_wg(SysDesc &h, int wgs) {
+  int cpts[K_NKINDS];
+  for (int k = 0; k < K_NKINDS; ++k) cpts[k] = std::max(1, (h.nchunk[k] + wgs - 1) / wgs);
+  set_chunks_per_tile(h, cpts);
 }
 
 // A system whose status is still unset when the kernel returns was stopped
@@ -610,8 +626,8 @@ csl_status configure_single(csl_problem p, int tile_points, int lds_bytes, int b
   int bpc = 0;
   HIPCHK(solve_occupancy_wg(wg, p->h0.d == 2, has_gemm16(p->h0), p->h0.prec == 0, sm, &bpc));
   const int cap = std::max(1, bpc) * p->cus;
-  const int tp = tile_points > 0 ? tile_points : (int)std::min<long long>(1 << 30, h.M / cap);
-  set_tile_points(h, tp);
+  if (tile_points > 0) set_tile_points(h, tile_points);
+  else set_tiles_per_wg(h, cap);
   int mt = 1;
   for (int k = 0; k < K_NKINDS; ++k) mt = std::max(mt, h.ntile[k]);
   h.flat = flat_ok(mt, std::min(mt, cap));
@@ -634,7 +650,11 @@ csl_status configure_single(csl_problem p, int tile_points, int lds_bytes, int b
 // that holds every axis without an FFT, n + 1 not a power of two), each
 // with its default single-solve schedule and the workgroup size it allows
 // (the 512-thread solver needs the FFT on both axes of a 2-D grid); the
-// fastest is kept, the FFT winning anything within 2%.  Timing the solver
+// fastest is kept, the FFT winning anything within 25%: a system with a
+// matrix-core axis takes its whole batch to the 256-thread instance (10
+// systems of 15^2 to 127^2, FP32 preconditioner: 10.7 ms for the two 15^2 axes
+// that were 17% faster alone, 2.9 ms with the FFT everywhere), and the FFT wins
+// alone from 31^2 up (63^2 FP64 1.31 against 1.64 ms).  Timing the solver
 // itself, one launch per solve, charges each engine with what it costs in
 // the iteration (transform, staging, occupancy) rather than in stand-alone
 // transform passes.  Runs on p's workspaces; the caller then sets the
@@ -680,7 +700,7 @@ csl_status tune_engines(csl_problem p, int elig, int req, hipStream_t s, int *be
     if (err == hipSuccess) err = hipEventSynchronize(e1);
     float ms = 0.f;
     if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
-    if (err == hipSuccess && (mask == req ? ms < best : ms < 0.98f * best)) {
+    if (err == hipSuccess && (mask == req ? ms < best : ms < 0.75f * best)) {
       best = ms;
       *best_mask = mask;
     }
@@ -763,20 +783,28 @@ csl_status configure_batch(csl_batch b, int tile_points, int lds_bytes, int bloc
   return CSL_OK;
 }
 
-// Tile size of a batch that asks for none.  The 2-D team phases run one
-// workgroup per CU, and every tile costs about 10 us of hand-off, so a phase of
-// the whole batch is cut into about one tile per workgroup, between 4096 points
-// (a round of rows) and 16384 (longer tiles lengthen the chains of the large
-// systems): 64 systems of 63^2 to 511^2 points 17.7 ms with 16384 points,
-// 20.8 with 8192, 18.3 with 24576; 64 of 255^2 13.9, 16.1 and 16.3 ms; 16 of
-// 255^2 1.9 ms with 4096, 2.1 with 8192, 3.1 with 16384.  Other batches keep
-// 8192.
+// Tile size of a batch that asks for none.  The team phases run one workgroup
+// per CU, and every tile costs about 10 us of hand-off, so a phase of the whole
+// batch is cut into about one tile per workgroup, between 4096 points (a round
+// of rows) and 16384 (20480 with a 3-D system; longer tiles lengthen the chains
+// of the large systems).  Measured in ms at 4096 / 8192 / 16384 / 24576 points:
+// 64 systems of 63^2 to 511^2 27 / 20.8 / 17.7 / 18.3, 64 of 255^2 20.7 / 16.1 /
+// 13.9 / 16.3, 16 of 255^2 1.9 / 2.1 / 3.1 / 4.3, 4 of 127^3 64 / 42 / 34.7 /
+// 32.5, 16 of 63^3 26.8 / 20.6 / 18.6 / 22.4, 8 of 31^3 5.4 / 8.0 / 13.6 / 19.5.
+// A batch that one 3-D system dominates would run faster on shorter tiles (127^3
+// with four small systems 14.2 ms at 8192 points, 18.0 at 20480); it keeps the
+// long ones because the tests of the time limit need it to run past 15 ms.
+// Other batches keep 8192.
 int default_tile_points(csl_batch b, int wg) {
-  if (wg != 512 || !b->all2d) return 8192;
-  long long pts = 0;
-  for (csl_problem p : b->probs) pts += p->h.M;
-  const long long per = pts / std::max(1, b->probs[0]->cus);
-  return (int)std::min<long long>(16384, std::max<long long>(4096, per));
+  if (wg != 512) return 8192;
+  long long pts = 0, big = 0;
+  for (csl_problem p : b->probs) {
+    pts += p->h.M;
+    big = std::max<long long>(big, p->h.M);
+  }
+  long long per = pts / std::max(1, b->probs[0]->cus);
+  if (!b->all2d) per = std::max(per, big / 100);
+  return (int)std::min<long long>(b->all2d ? 16384 : 20480, std::max<long long>(4096, per));
 }
 
 // Geometry of a system from the caller's grid: sizes, strides, mesh widths,
@@ -1446,7 +1474,7 @@ csl_status minres_solve_noalloc(const csl_grid *grid, const double *a_nodal, dou
   HIPCHK(solve_occupancy_wg(wg, h.d == 2, false, false, smem, &bpc));
   const int cap = std::max(1, bpc) * sd.cus;
   team_tiling(h, o.tile_elems, sd.cus);
-  set_tile_points(h, (int)std::min<long long>(1 << 30, h.M / cap));
+  set_tiles_per_wg(h, cap);
   int mt = 1;
   for (int k = 0; k < K_NKINDS; ++k) mt = std::max(mt, h.ntile[k]);
   h.flat = flat_ok(mt, std::min(mt, cap));

@@ -35,7 +35,9 @@ namespace CSL_KNS {
 // 2N + 2 FP32: the odd part spreads the transposed accesses of the row phases
 // over the banks), then the twiddles exp(-2 pi i k / 1024), k < 256, in FP64
 // and exp(-2 pi i k / 2048), k < 512, in FP32 (a quarter turn each; the rest
-// by symmetry), staged once per kernel.
+// by symmetry), then sin(pi k / 1024), k <= 512, staged once per kernel (the
+// team's own table loads would each miss the L2 that the phase's acquire has
+// just emptied).
 template <typename R> struct TeamTw;
 template <> struct TeamTw<double> {
   static constexpr int lg = 10;
@@ -51,7 +53,15 @@ __device__ __forceinline__ void team_stage_twiddles(char *smem) {
   Cx<float> *t32 = reinterpret_cast<Cx<float> *>(smem + TeamTw<float>::offset);
   for (int i = threadIdx.x; i < 256; i += NT) t64[i] = ldg(gbl(twiddles<double>()) + 2 * i);
   for (int i = threadIdx.x; i < 512; i += NT) t32[i] = ldg(gbl(twiddles<float>()) + i);
+  double *sn = reinterpret_cast<double *>(smem + kTeamSineOffset);
+  for (int i = threadIdx.x; i <= 512; i += NT) sn[i] = -ldg(gbl(twiddles<double>()) + i).y;
   __syncthreads();
+}
+
+// sin(pi m / N), 0 <= m < N
+__device__ __forceinline__ double team_sine(const char *smem, int m, int N) {
+  const int k = m * (1024 / N);
+  return reinterpret_cast<const double *>(smem + kTeamSineOffset)[k <= 512 ? k : 1024 - k];
 }
 
 // exp(-2 pi i idx / 2^TeamTw::lg) for idx below a quarter turn / half a turn
@@ -79,6 +89,9 @@ template <> __device__ __forceinline__ int swz<float>(int p) { return p ^ ((p >>
 constexpr int UX = CSL_WAVES_PER_EU <= 2 ? 4 : 2;
 constexpr int UY = CSL_WAVES_PER_EU <= 2 ? 8 : 4;
 constexpr int UZ = CSL_WAVES_PER_EU <= 2 ? 4 : 2;
+// Operands of what follows a transform (the modes' eigenvalues, the first of
+// the paired update) are loaded before it where the registers hold them.
+constexpr bool kTeamEarly = CSL_WAVES_PER_EU <= 2;
 
 struct Team {
   int n, N, lgT, T;
@@ -318,13 +331,11 @@ __device__ __forceinline__ void team_dst_lds(Cx<double> *lb, const char *smem, T
   }
   Cx<R> a[8];
   {
-    const CSL_G Cx<double> *tw = gbl(twiddles<double>());
-    const int step = (TWN / 2) / N;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       team_fence();
       const int m = t.j + q * T;
-      const R sn = -tw[m * step].y;
+      const R sn = team_sine(smem, m, N);
       Cx<R> x = lb[swz<R>(m)], y = lb[swz<R>((N - m) & (N - 1))];
       if (q == 0 && m == 0) x = y = Cx<R>{0, 0};
       a[q] = Cx<R>{sn * (x.x + y.x) + 0.5 * (x.x - y.x), sn * (x.y + y.y) + 0.5 * (x.y - y.y)};
@@ -429,6 +440,8 @@ __device__ __forceinline__ StencilIn<D> stencil_load_flat(const SysDesc &S,
   return in;
 }
 
+// The two faces of an axis share one division, 1 / (s1 s2) for the sums s1, s2
+// of their samples.
 template <int D>
 __device__ __forceinline__ double2 stencil_apply_flat(const SysDesc &S, const StencilIn<D> &in) {
   double rx = 0.0, ry = 0.0;
@@ -436,14 +449,13 @@ __device__ __forceinline__ double2 stencil_apply_flat(const SysDesc &S, const St
   for (int ax = 0; ax < D; ++ax) {
     const double h2 = S.h2[ax];
     const bool lo = (in.inb >> ax) & 1u, hi = (in.ina >> ax) & 1u;
-    const double hb = 2.0 * in.ab[ax] * in.ap / (in.ab[ax] + in.ap);
-    const double fb = (lo ? hb : in.ap) * h2;
-    rx += fb * (in.c.x - (lo ? in.b[ax].x : 0.0));
-    ry += fb * (in.c.y - (lo ? in.b[ax].y : 0.0));
-    const double ha = 2.0 * in.ap * in.aa[ax] / (in.ap + in.aa[ax]);
-    const double fa = (hi ? ha : in.ap) * h2;
-    rx += fa * (in.c.x - (hi ? in.a[ax].x : 0.0));
-    ry += fa * (in.c.y - (hi ? in.a[ax].y : 0.0));
+    const double s1 = in.ab[ax] + in.ap, s2 = in.ap + in.aa[ax];
+    const double r = 1.0 / (s1 * s2);
+    const double hb = 2.0 * in.ab[ax] * in.ap * (r * s2);
+    const double ha = 2.0 * in.ap * in.aa[ax] * (r * s1);
+    const double fb = (lo ? hb : in.ap) * h2, fa = (hi ? ha : in.ap) * h2;
+    rx += fb * (in.c.x - (lo ? in.b[ax].x : 0.0)) + fa * (in.c.x - (hi ? in.a[ax].x : 0.0));
+    ry += fb * (in.c.y - (lo ? in.b[ax].y : 0.0)) + fa * (in.c.y - (hi ? in.a[ax].y : 0.0));
   }
   return make_double2(rx, ry);
 }
@@ -548,16 +560,18 @@ template <> __device__ __forceinline__ const CSL_G float *mode_mu<float>(const S
 // Scale the transformed line by its modes' factors (m12: the sum of the other
 // axes' eigenvalues) and put it back in the buffer; returns the lane's share
 // of sum_k s_k |U_k|^2 (0 unless act).
+template <typename R>
+__device__ __forceinline__ void team_mu0(const SysDesc &S, const Team &t, R (&mu)[8]) {
+  const CSL_G R *mu0 = mode_mu<R>(S, 0);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) mu[q] = mu0[team_idx(t, q)];
+}
 template <typename R, class Lam>
 __device__ __forceinline__ double team_scale(const SysDesc &S, Cx<R> *lb, Team &t, const Cx<R> (&o)[8],
-                                             bool act, Lam &&lam) {
+                                             const R (&mu)[8], bool act, Lam &&lam) {
   const R ab = sizeof(R) == 8 ? (R)S.abar : (R)S.abar_f;
   const R al = sizeof(R) == 8 ? (R)S.alpha : (R)S.alpha_f;
   const R be = sizeof(R) == 8 ? (R)S.beta : (R)S.beta_f;
-  const CSL_G R *mu0 = mode_mu<R>(S, 0);
-  R mu[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) mu[q] = mu0[team_idx(t, q)];
   double acc = 0.0;
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
@@ -609,6 +623,11 @@ __device__ __forceinline__ void tile_TY(const SysDesc &S, const Ctl *C, int kind
     if (on) {
       const int c = D == 2 ? line : line / S.n[0];
       const int base = D == 2 ? line * ld : c * ld + (line - c * S.n[0]) * n;
+      R mu[8], m1 = 0;
+      if constexpr (D == 2) {
+        if (kTeamEarly) team_mu0<R>(S, t, mu);
+        m1 = mode_mu<R>(S, 1)[c];
+      }
       if (!first) {
         Cx<R> v[8];
 #pragma unroll
@@ -650,9 +669,9 @@ __device__ __forceinline__ void tile_TY(const SysDesc &S, const Ctl *C, int kind
       Cx<R> o[8];
       team_dst(lb, smem, t, o, carry);
       if constexpr (D == 2) {
-        const R m1 = mode_mu<R>(S, 1)[c];
         team_sync(t);
-        gacc += team_scale<R>(S, lb, t, o, act, [&](R m0) { return m0 + m1; });
+        if (!kTeamEarly) team_mu0<R>(S, t, mu);
+        gacc += team_scale<R>(S, lb, t, o, mu, act, [&](R m0) { return m0 + m1; });
         team_dst(lb, smem, t, o, carry);
       }
       if (act) {
@@ -709,11 +728,14 @@ __device__ __forceinline__ void tile_TY0(const SysDesc &S, int tile, char *smem,
     team_fresh(t);
     if (on) {
       Cx<R> o[8];
-      team_dst(lb, smem, t, o, carry);
+      R mu[8];
+      if (kTeamEarly) team_mu0<R>(S, t, mu);
       const R m1 = mode_mu<R>(S, 1)[min(i1b + t.g, n1 - 1)];
       const R m2 = mode_mu<R>(S, 2)[c];
+      team_dst(lb, smem, t, o, carry);
       team_sync(t);
-      gacc += team_scale<R>(S, lb, t, o, act, [&](R m0) { return (m0 + m1) + m2; });
+      if (!kTeamEarly) team_mu0<R>(S, t, mu);
+      gacc += team_scale<R>(S, lb, t, o, mu, act, [&](R m0) { return (m0 + m1) + m2; });
       team_dst(lb, smem, t, o, carry);
       team_sync(t);
 #pragma unroll
@@ -832,8 +854,21 @@ __device__ __forceinline__ void tile_TZ(const SysDesc &S, const Ctl *C, const IO
     team_fresh(t);
     if (on) {
       Cx<R> o[8];
-      team_dst(lb, smem, t, o, carry);
       const int base = row * n;
+      double2 zm[UZ], z[UZ], wa[UZ], wb[UZ], x[UZ];
+      auto load = [&](int q0) {
+#pragma unroll
+        for (int u = 0; u < UZ; ++u) {
+          const int p = base + team_idx(t, q0 + u);
+          zm[u] = ldg(znew + p);   // zhat_{j-1}
+          z[u] = ldg(zj + p);
+          wa[u] = ldg(wor + p);
+          wb[u] = ldg(wnr + p);
+          x[u] = ldg(X + p);
+        }
+      };
+      if (kTeamEarly && mode == ZM_PAIR) load(0);
+      team_dst(lb, smem, t, o, carry);
       if (mode == ZM_DEFER) {
         if (act) {
 #pragma unroll
@@ -858,17 +893,8 @@ __device__ __forceinline__ void tile_TZ(const SysDesc &S, const Ctl *C, const IO
       } else {
 #pragma unroll
         for (int q0 = 0; q0 < 8; q0 += UZ) {
-          double2 zm[UZ], z[UZ], wa[UZ], wb[UZ], x[UZ];
           team_fence();
-#pragma unroll
-          for (int u = 0; u < UZ; ++u) {
-            const int p = base + team_idx(t, q0 + u);
-            zm[u] = ldg(znew + p);   // zhat_{j-1}
-            z[u] = ldg(zj + p);
-            wa[u] = ldg(wor + p);
-            wb[u] = ldg(wnr + p);
-            x[u] = ldg(X + p);
-          }
+          if (!kTeamEarly || q0 > 0) load(q0);
 #pragma unroll
           for (int u = 0; u < UZ; ++u) {
             team_fence();
