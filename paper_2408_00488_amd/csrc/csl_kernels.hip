@@ -1619,8 +1619,9 @@ __device__ __forceinline__ void epilogue(const SysDesc &S, const SolveParams &P,
 // 256 workgroups before (511^2, FP64).
 // A slot is two words, each half a partial beside the 32-bit phase number, so
 // a word is valid by itself; two sets of slots alternate, because a workgroup
-// may mark the next phase while another still reads this one (it cannot get
-// two ahead: that needs the other's mark of the next).
+// may mark the next phase while another still reads this one.  It cannot get
+// two ahead: that needs the other's mark of the next, which a workgroup also
+// leaves (in the slot of its number) where a phase has no tile for it.
 // Every workgroup of the grid is resident here (it has been counted), so the
 // wait ends; the time limit bounds it as well: past it a workgroup raises
 // G->error, and those that wait for it leave too.
@@ -1633,18 +1634,19 @@ __shared__ Ctl s_ctl;
 __device__ __forceinline__ int flat_phase_end(const SysDesc &S, const SolveParams &P, Glob *G, int kind,
                                               int iter, int no, const double *own_part, unsigned seq,
                                               long long t0, double *red, int *sh_next) {
-  const int tid = threadIdx.x, nt = S.ntile[kind];
-  const int sg = (int)gridDim.x, own = xcd_tile((int)blockIdx.x, sg);
+  const int sg = (int)gridDim.x, tid = threadIdx.x, nt = max(S.ntile[kind], sg);
+  const int own = xcd_tile((int)blockIdx.x, sg);
   unsigned long long *slots = S.slots + (size_t)(seq & 1) * 2 * kFlatSlots;
   // one workgroup has nobody to meet: its barriers order its own writes and
   // reads (15^2 FP64: 1.09 ms through the slots)
   const bool alone = sg == 1;
   if (tid == 0) {
     sh_next[2] = 0;
-    if (no > 0 && !alone) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      for (int i = 0; i < no; ++i) {
-        const unsigned long long v = (unsigned long long)__double_as_longlong(own_part[i]);
+    if (!alone) {
+      if (no > 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      for (int i = 0; i < max(no, 1); ++i) {
+        const unsigned long long v =
+            no > 0 ? (unsigned long long)__double_as_longlong(own_part[i]) : 0ull;
         unsigned long long *w = slots + 2 * (own + i * sg);
         const unsigned long long mark = (unsigned long long)seq << 32;
         __hip_atomic_store(w, mark | (v >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1693,6 +1695,12 @@ __device__ __forceinline__ int flat_phase_end(const SysDesc &S, const SolveParam
   __syncthreads();
   return sh_next[0];
 }
+
+// Wait until the wave's stores have reached the L2.  A workgroup barrier does
+// not (it orders the workgroup's own view only), and the release fence that
+// follows it in one wave waits for that wave's stores alone: without this wait
+// its write-back could pass over lines still on their way.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ---------------------------------------------------------------------------
 // Persistent solver: every workgroup repeatedly claims a tile of whichever
@@ -1857,13 +1865,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
         if (tid == 0) own_part[fdone] = red[NT / 64];
         ++fdone;
         ftile += sg;
-        // every wave's stores are complete at the barrier
+        if (ftile >= S.ntile[kind]) stores_done();
         __syncthreads();
         continue;
       }
       // every wave's stores are complete at the barrier; one agent-scope
       // release fence then publishes them with the (relaxed) completion
       // count, and only the workgroup that completes the phase acquires
+      stores_done();
       __syncthreads();
       if (tid == 0) {
         S.part[tile] = red[NT / 64];
