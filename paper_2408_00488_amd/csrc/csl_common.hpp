@@ -145,11 +145,11 @@ constexpr int kFlatOwn = 8;
 
 // Team phases: LDS of the line buffers (4096 FP64 points in up to 64 lines, and
 // one 16-byte element of padding a line) and of the workgroup (the twiddles of
-// both precisions and a sine table behind them), lanes per line, lines a workgroup of 512
+// both precisions behind them), lanes per line, lines a workgroup of 512
 // threads holds, and the column stride.  Two workgroups fit a CU.
 constexpr int kTeamBufBytes = 65536 + 1024;
-constexpr int kTeamSineOffset = kTeamBufBytes + 8192;
-constexpr int kTeamLdsBytes = kTeamSineOffset + 513 * 8;
+constexpr int kTeamLds64Bytes = kTeamBufBytes + 512 * 16;   // FP64 alone
+constexpr int kTeamLdsBytes = kTeamLds64Bytes + 512 * 8;
 __host__ __device__ inline int team_lanes(int n) { return n >= 7 ? (n + 1) / 8 : 1; }
 __host__ __device__ inline int team_lines(int n) {
   const int g = 512 / team_lanes(n);

@@ -1197,20 +1197,20 @@ __device__ __forceinline__ void tile_YP(const SysDesc &S, const Ctl *C, int iter
 #if CSL_TEAM
 template <int D>
 __device__ __forceinline__ void team_tile(const SysDesc &S, const Ctl *C, const IOPtr &io, int kind, int iter, int tile,
-                                          char *smem, double *red, double *carry) {
+                                          char *smem, double *red) {
   if (kind == K_X) {
-    tile_TX<D>(S, io, iter, tile, smem, red, carry);
+    tile_TX<D>(S, io, iter, tile, smem, red);
   } else if (kind == K_Z) {
-    if (S.prec) tile_TZ<float, D>(S, C, io, iter, tile, smem, carry);
-    else tile_TZ<double, D>(S, C, io, iter, tile, smem, carry);
+    if (S.prec) tile_TZ<float, D>(S, C, io, iter, tile, smem);
+    else tile_TZ<double, D>(S, C, io, iter, tile, smem);
   } else if (kind == K_PR) {
     tile_PR<D>(S, io, tile, red);
   } else if (D == 3 && kind == K_Y) {
-    if (S.prec) tile_TY0<float>(S, tile, smem, red, carry);
-    else tile_TY0<double>(S, tile, smem, red, carry);
+    if (S.prec) tile_TY0<float>(S, tile, smem, red);
+    else tile_TY0<double>(S, tile, smem, red);
   } else {
-    if (S.prec) tile_TY<float, D>(S, C, kind, iter, tile, smem, red, carry);
-    else tile_TY<double, D>(S, C, kind, iter, tile, smem, red, carry);
+    if (S.prec) tile_TY<float, D>(S, C, kind, iter, tile, smem, red);
+    else tile_TY<double, D>(S, C, kind, iter, tile, smem, red);
   }
 }
 #endif
@@ -1219,12 +1219,11 @@ template <int LDSB>
 __device__ __forceinline__ void process_tile(const SysDesc &S, const Ctl *C, const IOPtr &io, int kind, int iter,
                                              int tile, char *smem, double *red) {
 #if CSL_TEAM
-  __shared__ double carry[2 * (NT / 64)];
 #if CSL_2D_FFT_ONLY
-  team_tile<2>(S, C, io, kind, iter, tile, smem, red, carry);
+  team_tile<2>(S, C, io, kind, iter, tile, smem, red);
 #else
-  if (S.d == 3) team_tile<3>(S, C, io, kind, iter, tile, smem, red, carry);
-  else team_tile<2>(S, C, io, kind, iter, tile, smem, red, carry);
+  if (S.d == 3) team_tile<3>(S, C, io, kind, iter, tile, smem, red);
+  else team_tile<2>(S, C, io, kind, iter, tile, smem, red);
 #endif
   return;
 #else
@@ -1722,7 +1721,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
   __shared__ double own_part[kFlatOwn];
   const int tid = threadIdx.x;
 #if CSL_TEAM
-  team_stage_twiddles(smem);
+  team_stage_twiddles<true>(smem);
 #else
   twiddle_cache_reset();
 #endif

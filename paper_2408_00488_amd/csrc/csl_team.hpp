@@ -4,22 +4,29 @@
 // 1 below N = 8), eight points a lane: lane j holds the points m = j + q T, q <
 // 8.  Lines of up to 511 points fit a wave, so their teams exchange values
 // through LDS with no workgroup barrier (1023 points: two waves and a
-// barrier).  A pass through registers is a radix-8 (FP32: radix-16) Stockham
-// stage, so a line of 511 points meets LDS between three stages instead of
+// barrier).  A pass through registers is a radix-8 (the first: radix-16)
+// Stockham stage, so a line of 511 points meets LDS between three stages instead of
 // five, and the waves of a workgroup run independently: the loads and stores
 // of one run under the transforms of the others.  (With the workgroup-wide
 // radix-4 transform in its place every chunk waited at ten barriers.)
 //
 //   FP32: the odd extension, an FFT of 2N points with 16 values a lane.  Its
 //     first stage folds the extension: x_{m+N} = -x_{N-m}.
-//   FP64: an FFT of N points of the combined line
-//       y_m = sin(pi m / N) (x_m + x_{N-m}) + (x_m - x_{N-m}) / 2,
-//     whose outputs give S_{2m} = i (Y_m - Y_{N-m}) / 2 and the running sum
-//     S_{2m+1} = S_{2m-1} + (Y_m + Y_{N-m}) / 2, S_1 = Y_0 / 2 (S_k the
-//     unnormalised sine sums; every step is linear with real coefficients
-//     apart from the factor i, so it holds for complex lines).  The running
-//     sum's rounding stays at the level of the FFT's in FP64; in FP32 it
-//     would not (2-7e-7 against 4e-8), so FP32 keeps the odd extension.
+//   FP64: the first stage's outputs a = 1 .. 7 (mod 16) and their mirror
+//     images 16 - a give every X_k but those with k a multiple of 8, through
+//     seven FFTs of T points with half-integer frequencies.  The multiples of
+//     8 are the DST-I of T - 1 points x' of the folded line, taken as an eighth
+//     FFT of T points of the combined line
+//       y_j = sin(pi j / T) (x'_j + x'_{T-j}) + (x'_j - x'_{T-j}) / 2:
+//     S_{2m} = i (Y_m - Y_{T-m}) / 2 and the running sum S_{2m+1} = S_{2m-1} +
+//     (Y_m + Y_{T-m}) / 2, S_1 = Y_0 / 2.  So a lane holds 8 values where the
+//     whole extension takes 16.  The running sum's rounding grows with the
+//     square root of its length: with the whole line combined P^{-1} was off by
+//     1.9e-14 at 1023^2 (odd extension: 0.9e-15); over T / 2 <= 64 terms of an
+//     eighth of the outputs, closed by S_{T-1} = -Y_{T/2} / 2, it is 1.0e-15
+//     (511^2: 0.9e-15 against 1.0e-15).  255^3: 73.4 -> 72.5 ms, 1023^2: 1.60 ->
+//     1.58 ms.  In FP32 the sum would show (1.5e-7 against 1.1e-7 a transform
+//     of 511 points), for no time gained, so FP32 takes the extension.
 //
 // The vectors Tq, Tv and T are stored column by column: element (row, c) at
 // c ld + row, ld = S.ld an odd multiple of 8 (so that the 128-byte runs of
@@ -33,49 +40,37 @@ namespace CSL_KNS {
 
 // LDS of a workgroup: line buffers (line g at g LS elements, LS = N + 1 FP64,
 // 2N + 2 FP32: the odd part spreads the transposed accesses of the row phases
-// over the banks), then the twiddles exp(-2 pi i k / 1024), k < 256, in FP64
-// and exp(-2 pi i k / 2048), k < 512, in FP32 (a quarter turn each; the rest
-// by symmetry), then sin(pi k / 1024), k <= 512, staged once per kernel (the
-// team's own table loads would each miss the L2 that the phase's acquire has
-// just emptied).
-template <typename R> struct TeamTw;
-template <> struct TeamTw<double> {
-  static constexpr int lg = 10;
-  static constexpr int offset = kTeamBufBytes;
-};
-template <> struct TeamTw<float> {
-  static constexpr int lg = 11;
-  static constexpr int offset = kTeamBufBytes + 4096;
-};
+// over the banks), then the twiddles exp(-2 pi i k / 2048), k < 512, in FP64
+// and in FP32 (a quarter turn; the rest by symmetry), staged once per kernel
+// (the team's own table loads would each miss the L2 that the phase's acquire
+// has just emptied).
+constexpr int kTeamTwLg = 11;
+template <typename R> __device__ __forceinline__ const Cx<R> *team_tw(const char *smem) {
+  return reinterpret_cast<const Cx<R> *>(smem + kTeamBufBytes + (sizeof(R) == 8 ? 0 : 8192));
+}
 
+template <bool F32>
 __device__ __forceinline__ void team_stage_twiddles(char *smem) {
-  Cx<double> *t64 = reinterpret_cast<Cx<double> *>(smem + TeamTw<double>::offset);
-  Cx<float> *t32 = reinterpret_cast<Cx<float> *>(smem + TeamTw<float>::offset);
-  for (int i = threadIdx.x; i < 256; i += NT) t64[i] = ldg(gbl(twiddles<double>()) + 2 * i);
-  for (int i = threadIdx.x; i < 512; i += NT) t32[i] = ldg(gbl(twiddles<float>()) + i);
-  double *sn = reinterpret_cast<double *>(smem + kTeamSineOffset);
-  for (int i = threadIdx.x; i <= 512; i += NT) sn[i] = -ldg(gbl(twiddles<double>()) + i).y;
+  Cx<double> *t64 = const_cast<Cx<double> *>(team_tw<double>(smem));
+  Cx<float> *t32 = const_cast<Cx<float> *>(team_tw<float>(smem));
+  for (int i = threadIdx.x; i < 512; i += NT) {
+    t64[i] = ldg(gbl(twiddles<double>()) + i);
+    if (F32) t32[i] = ldg(gbl(twiddles<float>()) + i);
+  }
   __syncthreads();
 }
 
-// sin(pi m / N), 0 <= m < N
-__device__ __forceinline__ double team_sine(const char *smem, int m, int N) {
-  const int k = m * (1024 / N);
-  return reinterpret_cast<const double *>(smem + kTeamSineOffset)[k <= 512 ? k : 1024 - k];
-}
-
-// exp(-2 pi i idx / 2^TeamTw::lg) for idx below a quarter turn / half a turn
+// exp(-2 pi i idx / 2048) for idx below a quarter turn / half a turn
 template <typename R>
 __device__ __forceinline__ Cx<R> tw_q(const char *smem, int idx) {
-  return reinterpret_cast<const Cx<R> *>(smem + TeamTw<R>::offset)[idx];
+  return team_tw<R>(smem)[idx];
 }
 template <typename R>
 __device__ __forceinline__ Cx<R> tw_h(const char *smem, int idx) {
-  constexpr int Q = 1 << (TeamTw<R>::lg - 2);
+  constexpr int Q = 1 << (kTeamTwLg - 2);
   const Cx<R> w = tw_q<R>(smem, idx & (Q - 1));
   return idx < Q ? w : Cx<R>{w.y, -w.x};
 }
-
 // Position of element p of a line in its buffer: an XOR within aligned runs
 // of 128 bytes, so that the strided Stockham writes (8 or 16 elements between
 // lanes) fall on all banks; consecutive elements stay within their run.
@@ -171,9 +166,11 @@ __device__ __forceinline__ void dft8(Cx<R> (&x)[8]) {
 }
 
 // One Stockham stage of radix RAD on the lane's E values a[q] = element j + q
-// T: E / RAD butterflies b = j + s T of the elements b + p F / RAD (q = s + p E
-// / RAD), with the twiddles exp(-2 pi i k p / (RAD Ns)), k = b mod Ns.  Output
-// p of butterfly s replaces input p.
+// T of E T points: E / RAD butterflies b = j + s T of the elements b + p F / RAD
+// (q = s + p E / RAD), k = b mod Ns, with the twiddles exp(-2 pi i k' p / (RAD
+// Ns)).  k' = k for an FFT of the extended line (E = 16); k' = k - (k mod 8) / 2
+// after the folded first stage (E = 8), whose residues stand for half-integer
+// frequencies.
 template <typename R, int E, int RAD>
 __device__ __forceinline__ void team_stage(Cx<R> (&a)[E], const char *smem, int j, int T, int lgNs) {
   constexpr int S = E / RAD;
@@ -182,7 +179,7 @@ __device__ __forceinline__ void team_stage(Cx<R> (&a)[E], const char *smem, int 
   for (int s = 0; s < S; ++s) {
     team_fence();
     const int k = (j + s * T) & ((1 << lgNs) - 1);
-    const int i1 = k << (TeamTw<R>::lg - lgR - lgNs);
+    const int i1 = E == 8 ? (2 * k - (k & 7)) << (kTeamTwLg - 1 - lgR - lgNs) : k << (kTeamTwLg - lgR - lgNs);
     if constexpr (RAD == 8) {
       Cx<R> x[8];
       const Cx<R> w1 = tw_q<R>(smem, i1), w2 = tw_q<R>(smem, 2 * i1), w4 = tw_h<R>(smem, 4 * i1);
@@ -212,20 +209,23 @@ __device__ __forceinline__ void team_stage(Cx<R> (&a)[E], const char *smem, int 
   }
 }
 
-// The stages after the first (whose output p of lane j is element E j + p) of
-// an FFT of F = E T points: on return a[q] = output j + q T.  lb: the line's
-// buffer (F elements).
+// The stages after the first (whose output p of lane j is element E j + p): on
+// return a[q] = output j + q T.  lb: the line's buffer (E T elements).
+// Positions are formed by exclusive or: the lengths and strides are powers of
+// two, so the bits of the lane's part and of the (uniform) part of the value
+// never meet.
 template <typename R, int E>
 __device__ __forceinline__ void team_fft_rest(Cx<R> (&a)[E], Cx<R> *lb, const char *smem, Team &t) {
   if (t.T == 1) return;
   const int T = t.T;
-  constexpr int sm = sizeof(R) == 8 ? 7 : 15;
   team_sync(t);
+  const int w0 = swz<R>(E * t.j);
 #pragma unroll
-  for (int p = 0; p < E; ++p) lb[E * t.j + (p ^ (t.j & sm))] = a[p];   // swz(E j + p), E = sm + 1
+  for (int p = 0; p < E; ++p) lb[w0 ^ p] = a[p];
   team_sync(t);
+  const int r0 = swz<R>(t.j);
 #pragma unroll
-  for (int q = 0; q < E; ++q) a[q] = lb[swz<R>(t.j + q * T)];
+  for (int q = 0; q < E; ++q) a[q] = lb[r0 ^ swz<R>(q * T)];
   int lgNs = E == 8 ? 3 : 4, rem = t.lgT;
   for (; rem > 3; rem -= 3, lgNs += 3) {
     team_stage<R, E, 8>(a, smem, t.j, T, lgNs);
@@ -234,13 +234,14 @@ __device__ __forceinline__ void team_fft_rest(Cx<R> (&a)[E], Cx<R> *lb, const ch
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const int b = t.j + s * T, k = b & ((1 << lgNs) - 1);
-      const int base = ((b - k) << 3) + k;
+      const int w1 = swz<R>(((b - k) << 3) + k);
 #pragma unroll
-      for (int p = 0; p < 8; ++p) lb[swz<R>(base + (p << lgNs))] = a[s + p * S];
+      for (int p = 0; p < 8; ++p) lb[w1 ^ swz<R>(p << lgNs)] = a[s + p * S];
     }
     team_sync(t);
+    const int r1 = swz<R>(t.j);
 #pragma unroll
-    for (int q = 0; q < E; ++q) a[q] = lb[swz<R>(t.j + q * T)];
+    for (int q = 0; q < E; ++q) a[q] = lb[r1 ^ swz<R>(q * T)];
   }
   if (rem == 3) team_stage<R, E, 8>(a, smem, t.j, T, lgNs);
   else if (rem == 2) team_stage<R, E, 4>(a, smem, t.j, T, lgNs);
@@ -263,12 +264,51 @@ __device__ __forceinline__ void dst3(const Cx<R> *lb, Cx<R> (&o)[8]) {
   for (int q = 4; q < 8; ++q) o[q] = Cx<R>{0, 0};
 }
 
+// First stage, radix 16 on x_m and x_{m+N} = -x_{N-m} (m = j + q T): e[r] =
+// output 2r, from x_m - x_{N-m}; d[r] = output 2r + 1, from (x_m + x_{N-m})
+// exp(-2 pi i q / 16).  The line starts at swz(m) in its buffer.
+__device__ __forceinline__ void team_first(const Cx<double> *lb, const Team &t, Cx<double> (&e)[8],
+                                           Cx<double> (&d)[8]) {
+  typedef double R;
+  constexpr R c1 = (R)0.92387953251128675613, s1 = (R)0.38268343236508977173;
+  constexpr R h = (R)0.70710678118654752440;
+  const int T = t.T;
+  const bool first = t.j == 0;
+  const int r0 = swz<R>(t.j), m0 = swz<R>((T - t.j) & (T - 1));
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    // N - m = (T - j) + (7 - q) T (lane 0: (8 - q) T)
+    Cx<R> x = lb[r0 ^ swz<R>(q * T)];
+    Cx<R> y = lb[m0 ^ (first ? swz<R>(((8 - q) & 7) * T) : swz<R>((7 - q) * T))];
+    if (q == 0 && first) x = y = Cx<R>{0, 0};
+    e[q] = csub(x, y);
+    d[q] = cadd(x, y);
+  }
+  d[1] = cmul(d[1], Cx<R>{c1, -s1});
+  d[2] = Cx<R>{h * (d[2].x + d[2].y), h * (d[2].y - d[2].x)};
+  d[3] = cmul(d[3], Cx<R>{s1, -c1});
+  d[4] = mul_mi(d[4]);
+  d[5] = cmul(d[5], Cx<R>{-s1, -c1});
+  d[6] = Cx<R>{h * (d[6].y - d[6].x), -h * (d[6].x + d[6].y)};
+  d[7] = cmul(d[7], Cx<R>{-c1, -s1});
+  team_fence();
+  dft8(e);
+  team_fence();
+  dft8(d);
+  team_fence();
+}
+
+// 1 / sqrt(2 N), N = 8 T
+__device__ __forceinline__ double team_cf(const Team &t) {
+  const int lg = t.lgT + 4;
+  return ldexp((lg & 1) ? 0.70710678118654752440 : 1.0, -(lg >> 1));
+}
+
 // Orthonormal DST-I of the team's line, held in its buffer (x_m at swz(m), m =
 // 1 .. N - 1): o[q] = X_{j + q T} (o[0] of lane 0 is no output).  Starts by
 // ordering the team's writes of the line; the buffer may be written again by
 // the team once its outputs are used.
-__device__ __forceinline__ void team_dst(Cx<float> *lb, const char *smem, Team &t, Cx<float> (&o)[8],
-                                         double *) {
+__device__ __forceinline__ void team_dst(Cx<float> *lb, const char *smem, Team &t, Cx<float> (&o)[8]) {
   typedef float R;
   team_sync(t);
   if (t.N == 4) {
@@ -314,14 +354,11 @@ __device__ __forceinline__ void team_dst(Cx<float> *lb, const char *smem, Team &
   for (int q = 0; q < 8; ++q) o[q] = dst_out(a[q], cf);
 }
 
-// FP64: the outputs are left in the buffer (X_k at swz(k)); carry: one double2
-// per wave of the workgroup, for lines of more than a wave.
-__device__ __forceinline__ void team_dst_lds(Cx<double> *lb, const char *smem, Team &t,
-                                             double *carry) {
+// FP64: the outputs are left in the buffer (X_k at swz(k)).
+__device__ __forceinline__ void team_dst_lds(Cx<double> *lb, const char *smem, Team &t) {
   typedef double R;
   team_sync(t);
-  const int T = t.T, N = t.N;
-  if (N == 4) {
+  if (t.N == 4) {
     Cx<R> o[8];
     dst3<R>(lb, o);
     team_sync(t);
@@ -329,77 +366,71 @@ __device__ __forceinline__ void team_dst_lds(Cx<double> *lb, const char *smem, T
     for (int q = 1; q < 4; ++q) lb[swz<R>(q)] = o[q];
     return;
   }
+  const int T = t.T;
   Cx<R> a[8];
   {
+    Cx<R> e[8], d[8];
+    team_first(lb, t, e, d);
+    const R sn = -tw_h<R>(smem, t.j << (kTeamTwLg - 1 - t.lgT)).y;
+    a[0] = Cx<R>{sn * e[4].x + 0.5 * e[0].x, sn * e[4].y + 0.5 * e[0].y};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (r) a[2 * r] = e[r];
+      a[2 * r + 1] = d[r];
+    }
+  }
+  team_fft_rest<R, 8>(a, lb, smem, t);
+  team_sync(t);
+  const R cf = team_cf(t);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) a[q] = dst_out(a[q], q < 4 || T == 1 ? cf : -cf);
+  // output K = j + q T belongs to k = 16 (K / 8) + K mod 8, above N to 2N - k;
+  // those with K mod 8 = 0 wait at K
+  if (T >= 8) {
+    const bool z = (t.j & 7) == 0;
+    const int f = ((t.j >> 3) << 4) | (t.j & 7);
+    const int p0 = swz<R>(z ? t.j : f), p1 = swz<R>(z ? t.j : 2 * T - f);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      lb[(q < 4 ? p0 : p1) ^ (z ? swz<R>(q * T) : swz<R>((q < 4 ? q : 7 - q) * 2 * T))] = a[q];
+  } else {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      team_fence();
-      const int m = t.j + q * T;
-      const R sn = team_sine(smem, m, N);
-      Cx<R> x = lb[swz<R>(m)], y = lb[swz<R>((N - m) & (N - 1))];
-      if (q == 0 && m == 0) x = y = Cx<R>{0, 0};
-      a[q] = Cx<R>{sn * (x.x + y.x) + 0.5 * (x.x - y.x), sn * (x.y + y.y) + 0.5 * (x.y - y.y)};
+      const int K = t.j + q * T, k = 2 * K - (K & 7);
+      lb[swz<R>((K & 7) == 0 || T == 1 ? K : (k < t.N ? k : 2 * t.N - k))] = a[q];
     }
+    if (T == 1) return;
   }
-  dft8(a);
-  team_fft_rest<R, 8>(a, lb, smem, t);
-  // Y to the buffer; lane j takes m = 4j .. 4j + 3 and the partners N - m
+  // residue 0: X_{16 m} and X_{16 m + 8} (a running sum), m < T / 2, the real
+  // parts' sources in the lower half of the lanes, the imaginary in the upper;
+  // the last sum is Y_{T/2} too, and what the rounding leaves between the two is
+  // spread over the sums
   team_sync(t);
-#pragma unroll
-  for (int q = 0; q < 8; ++q) lb[swz<R>(t.j + q * T)] = a[q];
+  const int H = T >> 1, m = t.j & (H - 1), c = t.j >= H;
+  R *lr = reinterpret_cast<R *>(lb);
+  const R y = lr[2 * swz<R>(8 * m) + c];
+  R z = lr[2 * swz<R>((8 * (T - m)) & (8 * T - 1)) + c];
+  const R e = lr[2 * swz<R>(4 * T) + c];
+  if (m == 0) z = 0;
+  R run = c ? y - z : z - y;
+  for (int d = 1; d < H; d <<= 1) {
+    const R u = __shfl_up(run, (unsigned)d, H);
+    if (m >= d) run += u;
+  }
+  const R last = __shfl(run, H - 1, H);
+  run += ((c ? e : -e) - last) * ((m + 0.5) / H);
   team_sync(t);
-  const R cf = 1.0 / sqrt((R)(2 * N));
-  Cx<R> ev[4], od[4];
-  Cx<R> run = {0, 0};
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    team_fence();
-    const int m = 4 * t.j + u;
-    const Cx<R> y = lb[swz<R>(m)];
-    Cx<R> z = lb[swz<R>((N - m) & (N - 1))];
-    ev[u] = Cx<R>{-cf * (y.y - z.y), cf * (y.x - z.x)};
-    if (u == 0 && m == 0) z = Cx<R>{0, 0};
-    run = Cx<R>{run.x + cf * (y.x + z.x), run.y + cf * (y.y + z.y)};
-    od[u] = run;
-  }
-  // sum over the lanes before this one
-  Cx<R> in = run;
-  const int W = T < 64 ? T : 64;
-  const int jw = t.j & (W - 1);
-  for (int d = 1; d < W; d <<= 1) {
-    const R ux = __shfl_up(in.x, (unsigned)d, W), uy = __shfl_up(in.y, (unsigned)d, W);
-    if (jw >= d) {
-      in.x += ux;
-      in.y += uy;
-    }
-  }
-  Cx<R> off = {in.x - run.x, in.y - run.y};
-  if (T > 64) {
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 63) {
-      carry[2 * w] = in.x;
-      carry[2 * w + 1] = in.y;
-    }
-    __syncthreads();
-    if (t.j >= 64) {
-      off.x += carry[2 * (w - 1)];
-      off.y += carry[2 * (w - 1) + 1];
-    }
-  }
-  team_sync(t);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    lb[swz<R>(8 * t.j + 2 * u)] = ev[u];
-    lb[swz<R>(8 * t.j + 2 * u + 1)] = cadd(od[u], off);
-  }
+  if (m) lr[2 * swz<R>(16 * m) + c] = y + z;
+  lr[2 * swz<R>(16 * m + 8) + 1 - c] = run;
 }
 
-__device__ __forceinline__ void team_dst(Cx<double> *lb, const char *smem, Team &t,
-                                         Cx<double> (&o)[8], double *carry) {
-  team_dst_lds(lb, smem, t, carry);
+__device__ __forceinline__ void team_dst(Cx<double> *lb, const char *smem, Team &t, Cx<double> (&o)[8]) {
+  typedef double R;
+  team_dst_lds(lb, smem, t);
   team_sync(t);
+  const int r0 = swz<R>(t.j);
 #pragma unroll
-  for (int q = 0; q < 8; ++q) o[q] = lb[swz<double>(t.N == 4 ? (q & 3) : t.j + q * t.T)];
+  for (int q = 0; q < 8; ++q) o[q] = lb[t.N == 4 ? swz<R>(q & 3) : r0 ^ swz<R>(q * t.T)];
 }
 
 // Index of the point m = j + q T of a team's line, kept inside the line (lane 0
@@ -468,7 +499,7 @@ __device__ __forceinline__ double2 stencil_apply_flat(const SysDesc &S, const St
 // ---------------------------------------------------------------------------
 template <int D>
 __device__ __forceinline__ void tile_TX(const SysDesc &S, const IOPtr &io, int iter, int tile, char *smem,
-                                        double *red, double *carry) {
+                                        double *red) {
   Team t = make_team<double>(S.n[D - 1]);
   const int G = S.lpt_x, lgG = ilog2i(G);
   Cx<double> *buf = reinterpret_cast<Cx<double> *>(smem);
@@ -525,7 +556,7 @@ __device__ __forceinline__ void tile_TX(const SysDesc &S, const IOPtr &io, int i
           }
         }
       }
-      team_dst_lds(lb, smem, t, carry);
+      team_dst_lds(lb, smem, t);
     }
     __syncthreads();
     const int R = min(G, r1 - rb);
@@ -592,7 +623,7 @@ __device__ __forceinline__ double team_scale(const SysDesc &S, Cx<R> *lb, Team &
 // ---------------------------------------------------------------------------
 template <typename R, int D>
 __device__ __forceinline__ void tile_TY(const SysDesc &S, const Ctl *C, int kind, int iter, int tile, char *smem,
-                                        double *red, double *carry) {
+                                        double *red) {
   constexpr int ax = D - 2;
   Team t = make_team<R>(S.n[ax]);
   const int G = S.lpt_s[ax];
@@ -667,12 +698,12 @@ __device__ __forceinline__ void tile_TY(const SysDesc &S, const Ctl *C, int kind
         }
       }
       Cx<R> o[8];
-      team_dst(lb, smem, t, o, carry);
+      team_dst(lb, smem, t, o);
       if constexpr (D == 2) {
         team_sync(t);
         if (!kTeamEarly) team_mu0<R>(S, t, mu);
         gacc += team_scale<R>(S, lb, t, o, mu, act, [&](R m0) { return m0 + m1; });
-        team_dst(lb, smem, t, o, carry);
+        team_dst(lb, smem, t, o);
       }
       if (act) {
 #pragma unroll
@@ -693,8 +724,7 @@ __device__ __forceinline__ void tile_TY(const SysDesc &S, const Ctl *C, int kind
 // lpt_s[0] neighbouring lines i1 of one column c, read and written by the
 // workgroup with i1 fastest and transformed by a team each.
 template <typename R>
-__device__ __forceinline__ void tile_TY0(const SysDesc &S, int tile, char *smem, double *red,
-                                         double *carry) {
+__device__ __forceinline__ void tile_TY0(const SysDesc &S, int tile, char *smem, double *red) {
   Team t = make_team<R>(S.n[0]);
   const int G = S.lpt_s[0], lgG = ilog2i(G);
   Cx<R> *buf = reinterpret_cast<Cx<R> *>(smem);
@@ -732,11 +762,11 @@ __device__ __forceinline__ void tile_TY0(const SysDesc &S, int tile, char *smem,
       if (kTeamEarly) team_mu0<R>(S, t, mu);
       const R m1 = mode_mu<R>(S, 1)[min(i1b + t.g, n1 - 1)];
       const R m2 = mode_mu<R>(S, 2)[c];
-      team_dst(lb, smem, t, o, carry);
+      team_dst(lb, smem, t, o);
       team_sync(t);
       if (!kTeamEarly) team_mu0<R>(S, t, mu);
       gacc += team_scale<R>(S, lb, t, o, mu, act, [&](R m0) { return (m0 + m1) + m2; });
-      team_dst(lb, smem, t, o, carry);
+      team_dst(lb, smem, t, o);
       team_sync(t);
 #pragma unroll
       for (int q = 0; q < 8; ++q) lb[swz<R>(t.j + q * t.T)] = o[q];
@@ -759,7 +789,7 @@ __device__ __forceinline__ void tile_TY0(const SysDesc &S, int tile, char *smem,
 // ---------------------------------------------------------------------------
 template <typename R, int D>
 __device__ __forceinline__ void tile_TZ(const SysDesc &S, const Ctl *C, const IOPtr &io, int iter, int tile,
-                                        char *smem, double *carry) {
+                                        char *smem) {
   Team t = make_team<R>(S.n[D - 1]);
   const int G = S.lpt_z, lgG = ilog2i(G);
   Cx<R> *buf = reinterpret_cast<Cx<R> *>(smem);
@@ -868,7 +898,7 @@ __device__ __forceinline__ void tile_TZ(const SysDesc &S, const Ctl *C, const IO
         }
       };
       if (kTeamEarly && mode == ZM_PAIR) load(0);
-      team_dst(lb, smem, t, o, carry);
+      team_dst(lb, smem, t, o);
       if (mode == ZM_DEFER) {
         if (act) {
 #pragma unroll
