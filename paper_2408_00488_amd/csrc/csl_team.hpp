@@ -264,6 +264,31 @@ __device__ __forceinline__ void dst3(const Cx<R> *lb, Cx<R> (&o)[8]) {
   for (int q = 4; q < 8; ++q) o[q] = Cx<R>{0, 0};
 }
 
+// n = 7 in FP64, held by one lane: the sums u_m = x_m + x_{8-m} give the odd
+// outputs, the differences v_m the even ones, X_k = 1/2 sum_m x_m sin(pi m k / 8)
+__device__ __forceinline__ void dst7(const Cx<double> *lb, Cx<double> (&o)[8]) {
+  constexpr double h = 0.70710678118654752440, c = 0.92387953251128675613, s = 0.38268343236508977173;
+  Cx<double> x[8];
+#pragma unroll
+  for (int m = 1; m < 8; ++m) x[m] = lb[m];   // swz(m) = m below 8
+  auto part = [&](auto get, auto put) {
+    const double u1 = get(x[1]) + get(x[7]), u2 = get(x[2]) + get(x[6]), u3 = get(x[3]) + get(x[5]);
+    const double v1 = get(x[1]) - get(x[7]), v2 = get(x[2]) - get(x[6]), v3 = get(x[3]) - get(x[5]);
+    const double u4 = get(x[4]), hu = h * u2, hv = h * (v1 + v3);
+    const double p = s * u1 + c * u3, q = c * u1 - s * u3;
+    put(o[1], 0.5 * ((p + hu) + u4));
+    put(o[7], 0.5 * ((p - hu) - u4));
+    put(o[3], 0.5 * ((q + hu) - u4));
+    put(o[5], 0.5 * ((q - hu) + u4));
+    put(o[2], 0.5 * (hv + v2));
+    put(o[6], 0.5 * (hv - v2));
+    put(o[4], 0.5 * (v1 - v3));
+  };
+  part([](const Cx<double> &a) { return a.x; }, [](Cx<double> &a, double b) { a.x = b; });
+  part([](const Cx<double> &a) { return a.y; }, [](Cx<double> &a, double b) { a.y = b; });
+  o[0] = Cx<double>{0, 0};
+}
+
 // First stage, radix 16 on x_m and x_{m+N} = -x_{N-m} (m = j + q T): e[r] =
 // output 2r, from x_m - x_{N-m}; d[r] = output 2r + 1, from (x_m + x_{N-m})
 // exp(-2 pi i q / 16).  The line starts at swz(m) in its buffer.
@@ -298,17 +323,22 @@ __device__ __forceinline__ void team_first(const Cx<double> *lb, const Team &t, 
   team_fence();
 }
 
-// 1 / sqrt(2 N), N = 8 T
-__device__ __forceinline__ double team_cf(const Team &t) {
+// 1 / sqrt(2 N), N = 8 T > 8.  Where it is not a power of two an inverse transform
+// takes sqrt(1/2) rounded down: the factors of a transform and its inverse are
+// the same for every value, and with both rounded up their product would be off
+// by 1.4e-16 (so: by -2e-17).
+__device__ __forceinline__ double team_cf(const Team &t, bool inverse) {
   const int lg = t.lgT + 4;
-  return ldexp((lg & 1) ? 0.70710678118654752440 : 1.0, -(lg >> 1));
+  const double h = inverse ? 0.70710678118654746 : 0.70710678118654757;
+  return ldexp((lg & 1) ? h : 1.0, -(lg >> 1));
 }
 
 // Orthonormal DST-I of the team's line, held in its buffer (x_m at swz(m), m =
 // 1 .. N - 1): o[q] = X_{j + q T} (o[0] of lane 0 is no output).  Starts by
 // ordering the team's writes of the line; the buffer may be written again by
 // the team once its outputs are used.
-__device__ __forceinline__ void team_dst(Cx<float> *lb, const char *smem, Team &t, Cx<float> (&o)[8]) {
+__device__ __forceinline__ void team_dst(Cx<float> *lb, const char *smem, Team &t, Cx<float> (&o)[8],
+                                         bool) {
   typedef float R;
   team_sync(t);
   if (t.N == 4) {
@@ -355,18 +385,20 @@ __device__ __forceinline__ void team_dst(Cx<float> *lb, const char *smem, Team &
 }
 
 // FP64: the outputs are left in the buffer (X_k at swz(k)).
-__device__ __forceinline__ void team_dst_lds(Cx<double> *lb, const char *smem, Team &t) {
+__device__ __forceinline__ void team_dst_lds(Cx<double> *lb, const char *smem, Team &t, bool inverse) {
   typedef double R;
   team_sync(t);
-  if (t.N == 4) {
+  if (t.N <= 8) {
     Cx<R> o[8];
-    dst3<R>(lb, o);
+    if (t.N == 4) dst3<R>(lb, o);
+    else dst7(lb, o);
     team_sync(t);
 #pragma unroll
-    for (int q = 1; q < 4; ++q) lb[swz<R>(q)] = o[q];
+    for (int q = 1; q < 8; ++q) lb[q] = o[q];
     return;
   }
   const int T = t.T;
+  const R cf = team_cf(t, inverse);
   Cx<R> a[8];
   {
     Cx<R> e[8], d[8];
@@ -381,9 +413,8 @@ __device__ __forceinline__ void team_dst_lds(Cx<double> *lb, const char *smem, T
   }
   team_fft_rest<R, 8>(a, lb, smem, t);
   team_sync(t);
-  const R cf = team_cf(t);
 #pragma unroll
-  for (int q = 0; q < 8; ++q) a[q] = dst_out(a[q], q < 4 || T == 1 ? cf : -cf);
+  for (int q = 0; q < 8; ++q) a[q] = dst_out(a[q], q < 4 ? cf : -cf);
   // output K = j + q T belongs to k = 16 (K / 8) + K mod 8, above N to 2N - k;
   // those with K mod 8 = 0 wait at K
   if (T >= 8) {
@@ -397,9 +428,8 @@ __device__ __forceinline__ void team_dst_lds(Cx<double> *lb, const char *smem, T
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int K = t.j + q * T, k = 2 * K - (K & 7);
-      lb[swz<R>((K & 7) == 0 || T == 1 ? K : (k < t.N ? k : 2 * t.N - k))] = a[q];
+      lb[swz<R>((K & 7) == 0 ? K : (k < t.N ? k : 2 * t.N - k))] = a[q];
     }
-    if (T == 1) return;
   }
   // residue 0: X_{16 m} and X_{16 m + 8} (a running sum), m < T / 2, the real
   // parts' sources in the lower half of the lanes, the imaginary in the upper;
@@ -424,9 +454,10 @@ __device__ __forceinline__ void team_dst_lds(Cx<double> *lb, const char *smem, T
   lr[2 * swz<R>(16 * m + 8) + 1 - c] = run;
 }
 
-__device__ __forceinline__ void team_dst(Cx<double> *lb, const char *smem, Team &t, Cx<double> (&o)[8]) {
+__device__ __forceinline__ void team_dst(Cx<double> *lb, const char *smem, Team &t, Cx<double> (&o)[8],
+                                         bool inverse) {
   typedef double R;
-  team_dst_lds(lb, smem, t);
+  team_dst_lds(lb, smem, t, inverse);
   team_sync(t);
   const int r0 = swz<R>(t.j);
 #pragma unroll
@@ -556,7 +587,7 @@ __device__ __forceinline__ void tile_TX(const SysDesc &S, const IOPtr &io, int i
           }
         }
       }
-      team_dst_lds(lb, smem, t);
+      team_dst_lds(lb, smem, t, false);
     }
     __syncthreads();
     const int R = min(G, r1 - rb);
@@ -698,12 +729,12 @@ __device__ __forceinline__ void tile_TY(const SysDesc &S, const Ctl *C, int kind
         }
       }
       Cx<R> o[8];
-      team_dst(lb, smem, t, o);
+      team_dst(lb, smem, t, o, kind == K_Y1I);
       if constexpr (D == 2) {
         team_sync(t);
         if (!kTeamEarly) team_mu0<R>(S, t, mu);
         gacc += team_scale<R>(S, lb, t, o, mu, act, [&](R m0) { return m0 + m1; });
-        team_dst(lb, smem, t, o);
+        team_dst(lb, smem, t, o, true);
       }
       if (act) {
 #pragma unroll
@@ -762,11 +793,11 @@ __device__ __forceinline__ void tile_TY0(const SysDesc &S, int tile, char *smem,
       if (kTeamEarly) team_mu0<R>(S, t, mu);
       const R m1 = mode_mu<R>(S, 1)[min(i1b + t.g, n1 - 1)];
       const R m2 = mode_mu<R>(S, 2)[c];
-      team_dst(lb, smem, t, o);
+      team_dst(lb, smem, t, o, false);
       team_sync(t);
       if (!kTeamEarly) team_mu0<R>(S, t, mu);
       gacc += team_scale<R>(S, lb, t, o, mu, act, [&](R m0) { return (m0 + m1) + m2; });
-      team_dst(lb, smem, t, o);
+      team_dst(lb, smem, t, o, true);
       team_sync(t);
 #pragma unroll
       for (int q = 0; q < 8; ++q) lb[swz<R>(t.j + q * t.T)] = o[q];
@@ -898,7 +929,7 @@ __device__ __forceinline__ void tile_TZ(const SysDesc &S, const Ctl *C, const IO
         }
       };
       if (kTeamEarly && mode == ZM_PAIR) load(0);
-      team_dst(lb, smem, t, o);
+      team_dst(lb, smem, t, o, true);
       if (mode == ZM_DEFER) {
         if (act) {
 #pragma unroll
