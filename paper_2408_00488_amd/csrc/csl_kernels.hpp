@@ -80,6 +80,16 @@ hipError_t solve_occupancy(size_t smem, int *blocks_per_cu);
 
 }  // namespace wg512p
 
+namespace pinv512 {
+
+// y = P^{-1} x in FP64 for a system with the FFT on every axis (descriptor h,
+// its copy dsys on the device): three passes in 2-D, five in 3-D.
+hipError_t upload_twiddles(const double2 *tw64, const float2 *tw32);
+hipError_t launch_pinv(const SysDesc *dsys, const SysDesc &h, int cus, const double2 *x, double2 *y,
+                       hipStream_t s);
+
+}  // namespace pinv512
+
 namespace wg512x {
 
 hipError_t upload_twiddles(const double2 *tw64, const float2 *tw32);
