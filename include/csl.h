@@ -97,8 +97,9 @@ enum {
 enum {
     CSL_DST_AUTO = 0,       /* per axis, the faster of FFT and GEMM, timed on
                                this device the first time a grid shape and
-                               precision is seen in the process (GEMM on
-                               every axis with n + 1 not a power of two)   */
+                               precision is seen in the process (GEMM where
+                               it is a quarter faster, and on every axis
+                               with n + 1 not a power of two)              */
     CSL_DST_FFT = 1,        /* FFT of the odd extension, staged in LDS
                                (CSL_ERR_ARG if an axis has n + 1 not a
                                power of two)                               */
@@ -175,8 +176,8 @@ csl_status problem_info(csl_problem p, double *abar, double *a_min,
  * tile_points grid points per scheduling tile (0 = about one tile per
  * workgroup and phase, which lets a single solve fill the device; 1 = one
  * LDS chunk per tile), the LDS line budget (0 or 32768 = default, 65536
- * = 64 KiB) and the workgroup size of the persistent solver, block_threads:
- * 0 = 512 where allowed, else 256; 256; 512, which is allowed for problems
+ * = 64 KiB; 512 threads always hold 64 KiB of lines) and the workgroup size
+ * of the persistent solver, block_threads: 0 = 512 where allowed, else 256; 256; 512, which is allowed for problems
  * whose sine transforms all run on the FFT (CSL_ERR_ARG otherwise); or 1024,
  * the plane phase, for 3-D problems with the FFT on every axis and n0, n1
  * <= 127 (CSL_ERR_ARG otherwise): one workgroup per CU holds the real or

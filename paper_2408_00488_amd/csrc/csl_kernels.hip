@@ -4,13 +4,13 @@
 // adjoint reduction and the coefficient set-up reductions.
 //
 // This file is the 256-thread instance (namespace csl::wg256).  It is also
-// compiled as two 512-thread instances of the persistent solver alone
-// (CSL_SOLVE_ONLY) for systems whose transforms all run on the LDS FFT:
-// csl_kernels_wg512.hip for 2-D ones (CSL_2D_FFT_ONLY) and
-// csl_kernels_wg512x.hip for either dimension (CSL_FFT_ONLY).  Eight waves
-// per workgroup at 128 registers keep twice the waves per CU in flight.
-// csl_kernels_wg256h.hip is a 256-thread solver with the FP16 split-product
-// sine-matrix engine (CSL_GEMM16) for the systems that use it.
+// compiled as instances of the persistent solver alone (CSL_SOLVE_ONLY):
+// csl_kernels_wg512.hip (CSL_2D_FFT_ONLY: 2-D systems) and
+// csl_kernels_wg512x.hip (either dimension) with the phases of csl_team.hpp
+// (CSL_TEAM) for systems whose transforms all run on the FFT,
+// csl_kernels_wg1024p.hip and csl_kernels_wg512p.hip with the plane phase
+// (CSL_PLANE), and csl_kernels_wg256h.hip, a 256-thread solver with the FP16
+// split-product sine-matrix engine (CSL_GEMM16) for the systems that use it.
 #include <math.h>
 
 #include "csl_device.hpp"
@@ -1227,10 +1227,7 @@ __device__ __forceinline__ void process_tile(const SysDesc &S, const Ctl *C, con
 #endif
   return;
 #else
-#if CSL_2D_FFT_ONLY
-  const bool d3 = false;
-  const bool g = false;
-#elif CSL_FFT_ONLY
+#if CSL_FFT_ONLY
   const bool d3 = (S.d == 3);
   const bool g = false;
 #else

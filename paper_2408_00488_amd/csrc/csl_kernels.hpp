@@ -1,12 +1,14 @@
 // Host-callable launch wrappers of the gfx950 kernels.  The device code is
-// built six times: csl::wg256 (256-thread workgroups; every kernel),
+// built six times as a solver: csl::wg256 (256-thread workgroups; every kernel),
 // csl::wg256h (the 256-thread persistent solver with the FP16 split-product
 // sine-matrix engine), csl::wg512 (512-thread workgroups; the persistent
-// solver for 2-D systems whose transforms all run on the LDS FFT),
+// solver for 2-D systems whose transforms all run on the FFT, a line per
+// team of lanes),
 // csl::wg512x (the same for FFT systems of either dimension), csl::wg1024p
 // (one 1024-thread workgroup per CU: the 3-D solver with the plane phase,
 // FP32 preconditioner) and csl::wg512p (one 512-thread workgroup per CU: the
-// same with the FP64 preconditioner).
+// same with the FP64 preconditioner).  csl::pinv512 holds the stand-alone
+// FP64 P^{-1} on the team transforms.
 #pragma once
 #include "csl_common.hpp"
 
