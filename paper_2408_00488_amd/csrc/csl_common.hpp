@@ -188,6 +188,24 @@ struct SolveParams {
   long long timeout_ticks;   // wall-clock ticks before idle workgroups abort
 };
 
+// Systems of one launch of the adjoint's reductions and of the conjugates.
+constexpr int kAdjGroup = 16;
+struct AdjGroup {
+  int count;
+  int nblk[kAdjGroup];
+  const SysDesc *sys[kAdjGroup];
+  const double2 *ytil[kAdjGroup], *z[kAdjGroup];
+  double2 *gf[kAdjGroup];
+  double *part[kAdjGroup];
+  double *galpha, *gbeta;   // of the group's first system, or null
+};
+struct ConjGroup {
+  int count;
+  int M[kAdjGroup];
+  const double2 *x[kAdjGroup];
+  double2 *y[kAdjGroup];
+};
+
 // Launch-wide state of a persistent solve.
 struct Glob {
   int active;          // systems not finished

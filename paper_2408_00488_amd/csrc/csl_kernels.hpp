@@ -29,10 +29,9 @@ hipError_t launch_apply_A(const SysDesc *dsys, int d, const int n[3], int M, con
                           double2 *y, hipStream_t s);
 hipError_t launch_pinv_pass(const SysDesc *dsys, int d, int prec, int pass, int ntile, size_t smem,
                             const double2 *x, double2 *y, hipStream_t s);
-hipError_t launch_adjoint(const SysDesc *dsys, int d, int M, const double2 *ytil,
-                          const double2 *z, double2 *gf, double *ga, double *part, int nblk,
-                          double *galpha, double *gbeta, hipStream_t s);
-hipError_t launch_conj(const double2 *x, double2 *y, int M, hipStream_t s);
+// Gradients of a group of systems of one dimension (of one grid if ga).
+hipError_t launch_adjoint(const AdjGroup &g, int d, double *ga, hipStream_t s);
+hipError_t launch_conj(const ConjGroup &g, hipStream_t s);
 // Step transform of an all-at-once vector (L = 2^lg steps of M points, 8 <= L
 // <= 1024): forward = DFT over the steps after the alpha^(k/L) scaling,
 // inverse = its inverse.

@@ -1647,6 +1647,16 @@ csl_status problem_tune(csl_problem p, const double *f, double *z, csl_batch_tun
   return CSL_OK;
 }
 
+// Entry j of a group of the adjoint's reductions.
+static void adjoint_entry(AdjGroup &g, int j, csl_problem p, const double *z, double *gf) {
+  g.nblk[j] = p->adj_nblk;
+  g.sys[j] = p->d_desc;
+  g.ytil[j] = p->ytmp;
+  g.z[j] = (const double2 *)z;
+  g.gf[j] = (double2 *)gf;
+  g.part[j] = p->adj_part;
+}
+
 csl_status minres_adjoint(csl_problem p, const double *z, const double *gz, double *gf,
                           double *galpha, double *gbeta, double *ga, const csl_solve_opts *opts,
                           csl_solve_info *info, hipStream_t s) {
@@ -1659,11 +1669,20 @@ csl_status minres_adjoint(csl_problem p, const double *z, const double *gz, doub
   const int M = p->h.M;
   // y = (K + conj(lambda) I)^{-1} G  <=>  A (block) u = conj(G) with u = y;
   // the solve stores conj(u) = conj(y) in ytmp.
-  HIPCHK(wg256::launch_conj((const double2 *)gz, p->gtmp, M, s));
+  ConjGroup cg{};
+  cg.count = 1;
+  cg.M[0] = M;
+  cg.x[0] = (const double2 *)gz;
+  cg.y[0] = p->gtmp;
+  HIPCHK(wg256::launch_conj(cg, s));
   csl_status st = run_single(p, p->gtmp, p->ytmp, P, s);
   if (st != CSL_OK) return st;
-  HIPCHK(wg256::launch_adjoint(p->d_desc, p->h.d, M, p->ytmp, (const double2 *)z, (double2 *)gf, ga,
-                        p->adj_part, p->adj_nblk, galpha, gbeta, s));
+  AdjGroup g{};
+  g.count = 1;
+  g.galpha = galpha;
+  g.gbeta = gbeta;
+  adjoint_entry(g, 0, p, z, gf);
+  HIPCHK(wg256::launch_adjoint(g, p->h.d, ga, s));
   if (!info) return CSL_OK;
   return fetch_single_info(p, info, s);
 }
@@ -1855,21 +1874,30 @@ csl_status batch_adjoint(csl_batch b, const double *const *z, const double *cons
                                     b->probs[0]->wall_khz);
   // y_j = (K + conj(lambda_j) I)^{-1} G_j for every system: the block system
   // with right-hand side conj(G_j), all systems in one persistent launch
-  for (int i = 0; i < b->count; ++i) {
-    const csl_problem p = b->probs[i];
-    HIPCHK(wg256::launch_conj((const double2 *)gz[i], p->gtmp, p->h.M, s));
+  for (int i0 = 0; i0 < b->count; i0 += kAdjGroup) {
+    ConjGroup g{};
+    g.count = std::min(kAdjGroup, b->count - i0);
+    for (int j = 0; j < g.count; ++j) {
+      g.M[j] = b->probs[i0 + j]->h.M;
+      g.x[j] = (const double2 *)gz[i0 + j];
+      g.y[j] = b->probs[i0 + j]->gtmp;
+    }
+    HIPCHK(wg256::launch_conj(g, s));
   }
   HIPCHK(wg256::launch_init(b->d_desc, b->count, b->glob, s));
   IOPtr none{nullptr, nullptr};
   HIPCHK(solve_launch(b->block_threads, b->all2d, b->g16, b->p64, b->d_desc, b->d_io_adj, none, b->count, P,
                       b->glob, b->grid, b->smem, s));
-  // gradients system by system, in order: ga accumulates the systems'
-  // coefficient gradients in a fixed order
-  for (int i = 0; i < b->count; ++i) {
-    const csl_problem p = b->probs[i];
-    HIPCHK(wg256::launch_adjoint(p->d_desc, p->h.d, p->h.M, p->ytmp, (const double2 *)z[i],
-                                 gf ? (double2 *)gf[i] : nullptr, ga, p->adj_part, p->adj_nblk,
-                                 galpha ? galpha + i : nullptr, gbeta ? gbeta + i : nullptr, s));
+  // gradients in groups of neighbouring systems of one dimension, in order: ga
+  // accumulates the systems' coefficient gradients in a fixed order
+  for (int i = 0; i < b->count;) {
+    AdjGroup g{};
+    const int d = b->probs[i]->h.d;
+    g.galpha = galpha ? galpha + i : nullptr;
+    g.gbeta = gbeta ? gbeta + i : nullptr;
+    for (; i < b->count && g.count < kAdjGroup && b->probs[i]->h.d == d; ++i, ++g.count)
+      adjoint_entry(g, g.count, b->probs[i], z[i], gf ? gf[i] : nullptr);
+    HIPCHK(wg256::launch_adjoint(g, d, ga, s));
   }
   if (!infos) return CSL_OK;
   std::vector<DevInfo> di(b->count);
