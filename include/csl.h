@@ -344,7 +344,8 @@ csl_status batch_solve(csl_batch b, const double *const *f, double *const *z,
  * dL/dRe z_j + i dL/dIm z_j (device, M_j complex each; host arrays of
  * `count` pointers).  The adjoint solves y_j = (K + conj(lambda_j) I)^{-1}
  * gz[j] of all systems run in one persistent launch (the batch's schedule),
- * then, system by system in order:
+ * then, with the results of one system after the other (so gf[j] may be z[i]
+ * of an earlier system i < j; gf[j] = z[j] is CSL_ERR_ARG):
  *   gf[j] = y_j (device, M_j complex, written; gf or any gf[j] may be NULL),
  *   galpha[j] = -Re(y_j^H z_j), gbeta[j] = Im(y_j^H z_j) (device arrays of
  *   `count` doubles, written; either may be NULL),

@@ -1647,6 +1647,12 @@ csl_status problem_tune(csl_problem p, const double *f, double *z, csl_batch_tun
   return CSL_OK;
 }
 
+// The byte ranges [a, a + na) and [b, b + nb) meet (a null one meets none).
+static bool ranges_meet(const void *a, size_t na, const void *b, size_t nb) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return a && b && x < y + nb && y < x + na;
+}
+
 // Entry j of a group of the adjoint's reductions.
 static void adjoint_entry(AdjGroup &g, int j, csl_problem p, const double *z, double *gf) {
   g.nblk[j] = p->adj_nblk;
@@ -1889,14 +1895,40 @@ csl_status batch_adjoint(csl_batch b, const double *const *z, const double *cons
   HIPCHK(solve_launch(b->block_threads, b->all2d, b->g16, b->p64, b->d_desc, b->d_io_adj, none, b->count, P,
                       b->glob, b->grid, b->smem, s));
   // gradients in groups of neighbouring systems of one dimension, in order: ga
-  // accumulates the systems' coefficient gradients in a fixed order
+  // accumulates the systems' coefficient gradients in a fixed order.  The
+  // systems of a group run side by side, so a group ends before a system whose
+  // vectors meet those of one in it (say gf[i] = z[j], j < i, whose z[j] is
+  // used up by then): results are those of one system after the other.
+  const size_t arr = sizeof(double) * b->count;
+  auto vec = [&](int i) { return sizeof(double2) * (size_t)b->probs[i]->h.M; };
+  auto gfi = [&](int i) { return gf ? (const void *)gf[i] : nullptr; };
+  // system i meets the arrays that all systems write, or those meet each other
+  const size_t gab = sizeof(double) * (size_t)b->probs[0]->h.M;
+  const bool shared = ranges_meet(galpha, arr, gbeta, arr) || ranges_meet(ga, gab, galpha, arr) ||
+                      ranges_meet(ga, gab, gbeta, arr);
+  auto alone = [&](int i) {
+    if (shared) return true;
+    for (const void *v : {(const void *)z[i], gfi(i)})
+      if (ranges_meet(v, vec(i), galpha, arr) || ranges_meet(v, vec(i), gbeta, arr) ||
+          ranges_meet(v, vec(i), ga, gab))
+        return true;
+    return false;
+  };
+  auto conflict = [&](int i, int j) {
+    return ranges_meet(gfi(i), vec(i), z[j], vec(j)) || ranges_meet(gfi(i), vec(i), gfi(j), vec(j)) ||
+           ranges_meet(z[i], vec(i), gfi(j), vec(j));
+  };
   for (int i = 0; i < b->count;) {
     AdjGroup g{};
-    const int d = b->probs[i]->h.d;
+    const int d = b->probs[i]->h.d, i0 = i;
     g.galpha = galpha ? galpha + i : nullptr;
     g.gbeta = gbeta ? gbeta + i : nullptr;
-    for (; i < b->count && g.count < kAdjGroup && b->probs[i]->h.d == d; ++i, ++g.count)
+    for (; i < b->count && g.count < kAdjGroup && b->probs[i]->h.d == d; ++i, ++g.count) {
+      bool end = i > i0 && (alone(i) || alone(i - 1));
+      for (int j = i0; j < i && !end; ++j) end = conflict(i, j);
+      if (end) break;
       adjoint_entry(g, g.count, b->probs[i], z[i], gf ? gf[i] : nullptr);
+    }
     HIPCHK(wg256::launch_adjoint(g, d, ga, s));
   }
   if (!infos) return CSL_OK;
