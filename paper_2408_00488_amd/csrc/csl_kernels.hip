@@ -1405,8 +1405,7 @@ __device__ __forceinline__ int xcd_tile(int b, int g) {
 // completion count, the scalars) before the new ticket word; on gfx950 an
 // agent-scope release writes back the L2, an acquire invalidates it, so no
 // fence beyond the one the protocol needs is issued.
-__device__ __forceinline__ void publish(const SysDesc &S, Ctl *C, int iter, int kind, bool flat) {
-  (void)S;
+__device__ __forceinline__ void publish(Ctl *C, int iter, int kind, bool flat) {
   __hip_atomic_store(&C->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t w = make_word(iter, kind) + (flat ? kWordFlat : 0ull);
   __hip_atomic_exchange(&C->word, (unsigned long long)w, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -1598,7 +1597,16 @@ __device__ __forceinline__ void epilogue(const SysDesc &S, const SolveParams &P,
       sg > 0 && __hip_atomic_load(&G->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= sg;
   const NextPhase n = advance(S, P, S.ctl, true, kind, iter, sum);
   if (n.kind == K_DONE) finish(S, G, n.iter, n.status, n.iters, n.rt);
-  else publish(S, S.ctl, n.iter, n.kind, flat);
+  else publish(S.ctl, n.iter, n.kind, flat);
+}
+
+// The epilogue as a function of its own, so that its registers are not the
+// kernel's where those are short (1024 threads, 128 registers: four 63^3 systems
+// 4.70 -> 4.55 ms, 127^3 alone 5.92 -> 5.60 ms in 30 steps).  With registers to
+// spare the call costs more than it gives (511^2 FP64 1.96 -> 2.06 ms).
+__device__ __attribute__((noinline)) void epilogue_call(const SysDesc &S, const SolveParams &P, int kind, int iter,
+                                                        Glob *G, double *red, int sg) {
+  epilogue(S, P, kind, iter, G, red, sg);
 }
 
 // ---------------------------------------------------------------------------
@@ -1707,8 +1715,17 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // workgroups exit when every system is done or the time limit passes; past
 // the limit no phase is published any more, so a system stops where it is
 // (status left unset) instead of running on in the workgroups still busy.
+// ONE is the kernel of a single system, with the flat solve; the kernel of a
+// batch has none of its state to carry through the phases (in one kernel for
+// both, four 63^3 systems on the plane phase, FP32, took 4.75 ms, now 4.55, and
+// 16 systems of 127^2 at 256 threads 7.31 ms, now 7.26).  SCAN is the search for
+// a tile among all systems, which a single system has no use for; its 2-D team
+// kernel keeps it all the same, because the compiler's registers come out
+// better with it (511^2 FP32 1.85 ms, 1.90 without; 1023^2 1.59 and 1.62), while
+// the others gain without it (127^3 FP32 on the plane phase 5.90 -> 5.60 ms in 30
+// steps, 31x63x15 2.55 -> 2.52).
 // ---------------------------------------------------------------------------
-template <int LDSB>
+template <int LDSB, bool ONE, bool SCAN = !ONE || CSL_2D_FFT_ONLY>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PER_EU))) void solve_kernel(
     const SysDesc *__restrict__ sys, const IOPtr *__restrict__ io, IOPtr io0, int nsys,
     SolveParams P, Glob *G) {
@@ -1732,15 +1749,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
   const int bcap = nsys > 1 ? 64 : 1;
   // a single system: once every workgroup has started, the next phase is
   // published flat, and every workgroup that sees it goes on flat
-  const int sg = nsys == 1 && sys[0].flat ? (int)gridDim.x : 0;
-  if (tid == 0) __hip_atomic_fetch_add(&G->arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int sg = ONE && sys[0].flat ? (int)gridDim.x : 0;
+  if (ONE && tid == 0)
+    __hip_atomic_fetch_add(&G->arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // flat solve: the phase, the next tile this workgroup owns of it, the tiles
   // it has done
   bool flat = false;
   int fkind = 0, fiter = 0, ftile = 0, fdone = 0;
   unsigned fseq = 0;
   for (;;) {
-    if (flat && ftile >= sys[0].ntile[fkind]) {
+    if (ONE && flat && ftile >= sys[0].ntile[fkind]) {
       fkind = flat_phase_end(sys[0], P, G, fkind, fiter, fdone, own_part, ++fseq, t0, red, sh_next);
       if (fkind < 0) break;
       fiter = sh_next[1];
@@ -1748,10 +1766,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
       fdone = 0;
       continue;
     }
-    if (!flat && tid < 64) {
+    if (!(ONE && flat) && tid < 64) {
       const int lane = tid;
       int found = -1;
-      if (sg > 0) {
+      if (!SCAN || sg > 0) {
         if (lane == 0) {
           const uint64_t w = __hip_atomic_load(&sys[0].ctl->word, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
@@ -1780,7 +1798,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
       // loads one ticket word, a ballot lists the systems with a tile ready,
       // and lanes try to claim one in order, starting from the last system
       // served.
-      for (int base = 0; sg == 0 && base < nsys && found == -1; base += 64) {
+      for (int base = 0; SCAN && sg == 0 && base < nsys && found == -1; base += 64) {
         const int k = base + lane;
         int sl = cur + k;
         while (sl >= nsys) sl -= nsys;
@@ -1837,9 +1855,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
       }
       if (lane == 0) sh_s = found;
     }
-    if (!flat) {
+    if (!(ONE && flat)) {
       __syncthreads();
-      if (sh_s == -3) {   // from here on flat; the acquire was taken above
+      if (ONE && sh_s == -3) {   // from here on flat; the acquire was taken above
         if (tid == 0) s_ctl = *sys[0].ctl;
         flat = true;
         fkind = sh_kind;
@@ -1849,15 +1867,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
         continue;
       }
     }
-    const int s = flat ? 0 : sh_s;
+    const int s = ONE && flat ? 0 : sh_s;
     if (s == -2) break;
     if (s >= 0) {
-      const int kind = flat ? fkind : sh_kind, iter = flat ? fiter : sh_iter;
-      const int tile = flat ? ftile : sh_tile;
-      const SysDesc &S = sys[s];
-      const IOPtr iop = io ? io[s] : io0;
-      process_tile<LDSB>(S, flat ? &s_ctl : S.ctl, iop, kind, iter, tile, smem, red);
-      if (flat) {
+      const int kind = ONE && flat ? fkind : sh_kind, iter = ONE && flat ? fiter : sh_iter;
+      const int tile = ONE && flat ? ftile : sh_tile;
+      const SysDesc &S = sys[SCAN ? s : 0];
+      const IOPtr iop = io ? io[SCAN ? s : 0] : io0;
+      process_tile<LDSB>(S, ONE && flat ? &s_ctl : S.ctl, iop, kind, iter, tile, smem, red);
+      if (ONE && flat) {
         if (tid == 0) own_part[fdone] = red[NT / 64];
         ++fdone;
         ftile += sg;
@@ -1888,7 +1906,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
         sh_last = last;
       }
       __syncthreads();
-      if (sh_last) epilogue(S, P, kind, iter, G, red, sg);
+      if (sh_last) {
+        if constexpr (NT == 1024) epilogue_call(S, P, kind, iter, G, red, ONE ? sg : 0);
+        else epilogue(S, P, kind, iter, G, red, ONE ? sg : 0);
+      }
     }
     __syncthreads();
   }
@@ -2395,44 +2416,59 @@ hipError_t upload_twiddles(const double2 *tw64, const float2 *tw32) {
   return hipMemcpyToSymbol(HIP_SYMBOL(g_tw32), tw32, sizeof(float2) * TWN);
 }
 
-hipError_t launch_solve(const SysDesc *dsys, const IOPtr *dio, IOPtr io0, int nsys,
-                        const SolveParams &P, Glob *G, int grid, size_t smem, hipStream_t s) {
+// Dynamic LDS of the solver on a line budget of LDSB bytes.
+template <int LDSB>
+static constexpr size_t solve_lds() {
 #if CSL_PLANE
-  // the plane phase uses the whole LDS (the row phases its first 72 KiB)
-  (void)smem;
-  hipLaunchKernelGGL(solve_kernel<65536>, dim3(grid), dim3(NT), kPlaneLdsBytes, s, dsys, dio, io0,
-                     nsys, P, G);
+  return kPlaneLdsBytes;   // the whole LDS (the row phases use its first 72 KiB)
 #elif CSL_TEAM
-  (void)smem;
-  hipLaunchKernelGGL(solve_kernel<65536>, dim3(grid), dim3(NT), kTeamLdsBytes, s, dsys, dio, io0,
-                     nsys, P, G);
+  return kTeamLdsBytes;
 #else
-  if (smem <= 32768)
-    hipLaunchKernelGGL(solve_kernel<32768>, dim3(grid), dim3(NT), 32768 + tw_lds_bytes(32768), s, dsys, dio,
+  return LDSB + tw_lds_bytes(LDSB);
+#endif
+}
+
+template <int LDSB>
+static hipError_t launch_solve_lds(const SysDesc *dsys, const IOPtr *dio, IOPtr io0, int nsys,
+                                   const SolveParams &P, Glob *G, int grid, hipStream_t s) {
+  if (nsys == 1)
+    hipLaunchKernelGGL((solve_kernel<LDSB, true>), dim3(grid), dim3(NT), solve_lds<LDSB>(), s, dsys, dio,
                        io0, nsys, P, G);
   else
-    hipLaunchKernelGGL(solve_kernel<65536>, dim3(grid), dim3(NT), 65536 + tw_lds_bytes(65536), s, dsys, dio,
+    hipLaunchKernelGGL((solve_kernel<LDSB, false>), dim3(grid), dim3(NT), solve_lds<LDSB>(), s, dsys, dio,
                        io0, nsys, P, G);
-#endif
   return hipGetLastError();
 }
 
-hipError_t solve_occupancy(size_t smem, int *blocks_per_cu) {
-#if CSL_PLANE
-  (void)smem;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, solve_kernel<65536>, NT,
-                                                      kPlaneLdsBytes);
-#elif CSL_TEAM
-  (void)smem;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, solve_kernel<65536>, NT,
-                                                      kTeamLdsBytes);
-#else
-  if (smem <= 32768)
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, solve_kernel<32768>, NT,
-                                                        32768 + tw_lds_bytes(32768));
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, solve_kernel<65536>, NT,
-                                                      65536 + tw_lds_bytes(65536));
+// Workgroups a CU holds of either kernel.
+template <int LDSB>
+static hipError_t solve_occupancy_lds(int *blocks_per_cu) {
+  int one = 0, many = 0;
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&one, solve_kernel<LDSB, true>, NT,
+                                                              solve_lds<LDSB>());
+  if (e == hipSuccess)
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&many, solve_kernel<LDSB, false>, NT,
+                                                     solve_lds<LDSB>());
+  *blocks_per_cu = one < many ? one : many;
+  return e;
+}
+
+// The plane and team instances have one line budget, 64 KiB.
+hipError_t launch_solve(const SysDesc *dsys, const IOPtr *dio, IOPtr io0, int nsys,
+                        const SolveParams &P, Glob *G, int grid, size_t smem, hipStream_t s) {
+#if !CSL_PLANE && !CSL_TEAM
+  if (smem <= 32768) return launch_solve_lds<32768>(dsys, dio, io0, nsys, P, G, grid, s);
 #endif
+  (void)smem;
+  return launch_solve_lds<65536>(dsys, dio, io0, nsys, P, G, grid, s);
+}
+
+hipError_t solve_occupancy(size_t smem, int *blocks_per_cu) {
+#if !CSL_PLANE && !CSL_TEAM
+  if (smem <= 32768) return solve_occupancy_lds<32768>(blocks_per_cu);
+#endif
+  (void)smem;
+  return solve_occupancy_lds<65536>(blocks_per_cu);
 }
 
 #if !CSL_SOLVE_ONLY
