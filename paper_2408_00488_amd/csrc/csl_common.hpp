@@ -127,8 +127,8 @@ struct SysDesc {
   double2 *W[2];           // search directions w_m, by parity of m
   double *part;            // per-tile partial sums
   unsigned long long *slots;   // per-tile arrivals of a flat solve: two sets (by phase
-                               // parity) of kFlatSlots slots of two words
-  int flat;                // the system's own solves may run flat
+                               // parity) of `flat` slots of two words
+  int flat;                // slots of a set if the system's own solves may run flat, else 0
   Ctl *ctl;
   DevInfo *info;
   // Lanczos coefficients of the last solve: lz[2 (j - 1)] = delta_j,
@@ -139,9 +139,11 @@ struct SysDesc {
 
 constexpr int kLanczosCap = 4096;
 
-// Tiles of a phase of a flat solve, at most, and tiles a workgroup owns of one.
-constexpr int kFlatSlots = 1024;
-constexpr int kFlatOwn = 8;
+// Tiles of a phase of a flat solve, at most, and tiles a workgroup owns of one
+// (their partials are held in LDS, of which the plane instances have 512 bytes
+// for all static variables).
+constexpr int kFlatSlots = 8192;
+constexpr int kFlatOwn = 16;
 
 // Team phases: LDS of the line buffers (4096 FP64 points in up to 64 lines, and
 // one 16-byte element of padding a line) and of the workgroup (the twiddles of

@@ -1640,7 +1640,7 @@ __device__ __forceinline__ int flat_phase_end(const SysDesc &S, const SolveParam
                                               long long t0, double *red, int *sh_next) {
   const int sg = (int)gridDim.x, tid = threadIdx.x, nt = max(S.ntile[kind], sg);
   const int own = xcd_tile((int)blockIdx.x, sg);
-  unsigned long long *slots = S.slots + (size_t)(seq & 1) * 2 * kFlatSlots;
+  unsigned long long *slots = S.slots + (size_t)(seq & 1) * 2 * S.flat;
   // one workgroup has nobody to meet: its barriers order its own writes and
   // reads (15^2 FP64: 1.09 ms through the slots)
   const bool alone = sg == 1;
@@ -1918,7 +1918,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
 #if !CSL_SOLVE_ONLY
 __global__ void init_kernel(const SysDesc *__restrict__ sys, int nsys, Glob *G) {
   if (nsys == 1 && sys[0].flat) {
-    for (int i = threadIdx.x; i < 4 * kFlatSlots; i += blockDim.x) sys[0].slots[i] = 0;
+    for (int i = threadIdx.x; i < 4 * sys[0].flat; i += blockDim.x) sys[0].slots[i] = 0;
   }
   for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
     Ctl *C = sys[s].ctl;

@@ -304,6 +304,7 @@ struct csl_problem_s {
   csl_problem_opts opts{};
   int single_te = 0;     // chunk size of the problem's own solves (0 = creation tiling)
   int part_cap = 1;      // per-tile partial-sum slots allocated
+  int slot_cap = 1;      // slots of a set of a flat solve allocated
 };
 
 // Grids up to this many points may take smaller chunks for their own solves
@@ -593,10 +594,14 @@ hipError_t launch_pinv_all(csl_problem p, const double2 *x, double2 *y, hipStrea
   return hipSuccess;
 }
 
-// A solve of at most mt tiles a phase on `grid` workgroups may run flat (see the
-// solver's flat solve): every tile has a slot, a workgroup owns a few tiles of a phase.
-int flat_ok(int mt, int grid) {
-  return mt <= kFlatSlots && mt <= kFlatOwn * std::max(1, grid) ? 1 : 0;
+// Slots a set of a flat solve (see there) of at most mt tiles a phase on `grid`
+// workgroups, given the slots of its workspace: one for every tile; 0 if it may
+// not run flat.  With more than a few tiles a workgroup too a flat solve is the
+// faster (30 steps of 127^3 FP64 at 256 threads, 2017 tiles of a chunk: 11.3 ms, with all
+// tiles claimed 36.8, with the first 512 owned 35.3; 15 x 15 x 1023 on the plane
+// phase 4.6 ms against 9.6 and 8.8).
+int flat_slots(int mt, int grid, int cap) {
+  return mt <= cap && mt <= kFlatOwn * std::max(1, grid) ? mt : 0;
 }
 
 // Schedule of a problem's own solves: the creation-time tiling with an LDS
@@ -634,7 +639,7 @@ csl_status configure_single(csl_problem p, int tile_points, int lds_bytes, int b
   else set_tiles_per_wg(h, cap);
   int mt = 1;
   for (int k = 0; k < K_NKINDS; ++k) mt = std::max(mt, h.ntile[k]);
-  h.flat = flat_ok(mt, std::min(mt, cap));
+  h.flat = flat_slots(mt, std::min(mt, cap), p->slot_cap);
   HIPCHK(hipMemcpyAsync(p->d_desc, &h, sizeof(SysDesc), hipMemcpyHostToDevice, s));
   HIPCHK(hipMemcpyAsync(p->d_desc0, &p->h0, sizeof(SysDesc), hipMemcpyHostToDevice, s));
   HIPCHK(hipStreamSynchronize(s));
@@ -969,8 +974,10 @@ static csl_status create_problem_impl(const csl_grid *grid, const double *a_noda
     choose_tiles(t, kSmallChunkElems[0], 0, &sm_t);
     part_cap = std::max(part_cap, t.maxtile);
   }
-  const size_t o_part = take(sizeof(double) * std::max(part_cap, team_max_tiles(h)));
-  const size_t o_slots = take(sizeof(unsigned long long) * 4 * kFlatSlots);
+  const int parts = std::max(part_cap, team_max_tiles(h));
+  const size_t o_part = take(sizeof(double) * parts);
+  p->slot_cap = std::min(kFlatSlots, parts);
+  const size_t o_slots = take(sizeof(unsigned long long) * 4 * p->slot_cap);
   const size_t o_ctl = take(sizeof(Ctl));
   const size_t o_info = take(sizeof(DevInfo));
   const size_t o_glob = take(sizeof(Glob));
@@ -1377,7 +1384,9 @@ csl_status minres_solve_noalloc(const csl_grid *grid, const double *a_nodal, dou
   const size_t o_stats = take(sizeof(double) * 4);
   const size_t o_spart = take(sizeof(double) * 4 * stats_nblk);
   const size_t o_part = take(sizeof(double) * std::max(h.maxtile, team_max_tiles(h)));
-  const size_t o_slots = take(sizeof(unsigned long long) * 4 * kFlatSlots);
+  // one tile a workgroup and phase: no more slots than workgroups
+  const int slot_cap = 1024;
+  const size_t o_slots = take(sizeof(unsigned long long) * 4 * slot_cap);
   const size_t o_lz = take(sizeof(double) * (2 * kLanczosCap + 1));
   const size_t o_mu = take(sizeof(double) * nmu);
   const size_t o_muf = take(sizeof(float) * nmu);
@@ -1481,7 +1490,7 @@ csl_status minres_solve_noalloc(const csl_grid *grid, const double *a_nodal, dou
   set_tiles_per_wg(h, cap);
   int mt = 1;
   for (int k = 0; k < K_NKINDS; ++k) mt = std::max(mt, h.ntile[k]);
-  h.flat = flat_ok(mt, std::min(mt, cap));
+  h.flat = flat_slots(mt, std::min(mt, cap), slot_cap);
   HIPCHK(wg256::launch_write_desc(h, d_desc, s));
   const SolveParams P = make_params(so.tol, so.maxit, so.check_true_residual, so.timeout_ms,
                                     sd.wall_khz);
