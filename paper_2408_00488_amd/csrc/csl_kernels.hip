@@ -1746,7 +1746,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CSL_WAVES_PE
   // workgroup idle between its phases, and one round (about 0.2 us) takes up
   // the next phase soonest; a batch keeps workgroups busy with other
   // systems, and polls less (about 14 us).
-  const int bcap = nsys > 1 ? 64 : 1;
+  const int bcap = ONE ? 1 : 64;
   // a single system: once every workgroup has started, the next phase is
   // published flat, and every workgroup that sees it goes on flat
   const int sg = ONE && sys[0].flat ? (int)gridDim.x : 0;
