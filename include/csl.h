@@ -97,9 +97,13 @@ enum {
 enum {
     CSL_DST_AUTO = 0,       /* per axis, the faster of FFT and GEMM, timed on
                                this device the first time a grid shape and
-                               precision is seen in the process (GEMM where
-                               it is a quarter faster, and on every axis
-                               with n + 1 not a power of two)              */
+                               precision is seen in the process (GEMM on
+                               every axis with n + 1 not a power of two).
+                               Batches and P^{-1} take GEMM on other axes only
+                               where it is a quarter faster, as one such axis
+                               sets the whole batch to 256 threads; so do the
+                               problem's own solves with an explicit
+                               block_threads of 512 or 1024                */
     CSL_DST_FFT = 1,        /* FFT of the odd extension, staged in LDS
                                (CSL_ERR_ARG if an axis has n + 1 not a
                                power of two)                               */

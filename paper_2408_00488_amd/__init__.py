@@ -259,6 +259,7 @@ class Problem:
         _check(load_library().problem_set_schedule(self.handle, int(tile_points), int(lds_bytes),
                                                    int(block_threads), int(tile_elems),
                                                    _stream(self.device)))
+        self._read_engines()   # 512 and 1024 threads take the FFT
 
     @property
     def schedule(self) -> dict:

@@ -167,6 +167,16 @@ bool has_gemm16(const SysDesc &h) { return h.gemm[0] == 2 || h.gemm[1] == 2 || h
 // The 512-thread solver applies: the FFT on every axis.
 bool fft_everywhere(const SysDesc &h) { return !h.gemm[0] && !h.gemm[1] && !h.gemm[2]; }
 bool fft_everywhere_mask(int m) { return (m & 7) == 0; }
+// Engines of the axes: the matrix product (code 1, or 2 for the FP16 split
+// products) on those of the mask.
+void set_engines(SysDesc &h, int mask, int code) {
+  for (int ax = 0; ax < 3; ++ax) h.gemm[ax] = ((mask >> ax) & 1) ? code : 0;
+}
+int engine_mask(const SysDesc &h) {
+  int m = 0;
+  for (int ax = 0; ax < 3; ++ax) m |= (h.gemm[ax] ? 1 : 0) << ax;
+  return m;
+}
 // The plane phase applies: 3-D, the FFT on every axis, lines of at most 127
 // points along the two leading axes and their plane (with the per-wave line
 // buffers and the twiddles) inside the instance's LDS: 16 waves with FP32
@@ -268,7 +278,10 @@ std::mutex g_scratch_mu;
 
 // Engine choices made by timing, per device and grid shape and precision.
 typedef std::tuple<int, int, int, int, int, int> ShapeKey;   // dev, d, n0, n1, n2, prec
-std::map<ShapeKey, int> g_engine_cache;                      // value: GEMM axis mask
+struct Engines {
+  int own, batch;   // GEMM axis masks: the problem's own solves; batches and P^{-1}
+};
+std::map<ShapeKey, Engines> g_engine_cache;
 std::mutex g_engine_mu;
 
 }  // namespace
@@ -293,13 +306,14 @@ struct csl_problem_s {
   size_t smem = 0;
   int grid1 = 1;
   int tile_elems = 0;
-  SysDesc h0{};          // creation-time tiling (one chunk per tile)
+  SysDesc h0{};          // creation-time tiling (one chunk per tile), engines of batches
+  int own_mask = 0;      // matrix-core axes of the problem's own solves
   size_t smem0 = 0;
   int cap = 1;           // workgroups that fill the device at this problem's LDS budget
   int tile_points = 0;   // current schedule of the problem's own solves
   int lds_bytes = 0;
   int block_threads = 256;
-  bool wg512_ok = false; // the FFT on every axis: the 512-thread solver applies
+  bool wg512_ok = false; // the FFT on every axis of h0: the 512-thread solver applies
   csl_grid grid{};       // creation arguments (for problem_clone)
   csl_problem_opts opts{};
   int single_te = 0;     // chunk size of the problem's own solves (0 = creation tiling)
@@ -613,6 +627,9 @@ csl_status configure_single(csl_problem p, int tile_points, int lds_bytes, int b
   SysDesc h = p->h0;
   size_t sm = p->smem0;
   const bool plane = block_threads == 1024;
+  // a workgroup size that needs the FFT on every axis takes it where batches do
+  if (!((block_threads == 512 || plane) && p->wg512_ok))
+    set_engines(h, p->own_mask, p->opts.dst_engine == CSL_DST_GEMM16 ? 2 : 1);
   if (plane) {
     if (!plane_ok(h))
       return fail(CSL_ERR_ARG, "block_threads 1024 (the plane phase) needs a 3-D problem with the "
@@ -627,13 +644,13 @@ csl_status configure_single(csl_problem p, int tile_points, int lds_bytes, int b
   }
   // every tile of every phase owns a partial-sum slot
   if (h.maxtile > p->part_cap) return fail(CSL_ERR_ARG, "chunking exceeds the partial-sum slots");
-  const int wg = resolve_wg(block_threads, p->wg512_ok);
+  const int wg = resolve_wg(block_threads, fft_everywhere(h));
   if (wg == 512) {
     team_tiling(h, p->single_te, p->cus);
     sm = 65536;
   }
   int bpc = 0;
-  HIPCHK(solve_occupancy_wg(wg, p->h0.d == 2, has_gemm16(p->h0), p->h0.prec == 0, sm, &bpc));
+  HIPCHK(solve_occupancy_wg(wg, h.d == 2, has_gemm16(h), h.prec == 0, sm, &bpc));
   const int cap = std::max(1, bpc) * p->cus;
   if (tile_points > 0) set_tile_points(h, tile_points);
   else set_tiles_per_wg(h, cap);
@@ -658,18 +675,19 @@ csl_status configure_single(csl_problem p, int tile_points, int lds_bytes, int b
 // persistent solver with every admissible subset of the eligible axes (one
 // that holds every axis without an FFT, n + 1 not a power of two), each
 // with its default single-solve schedule and the workgroup size it allows
-// (the 512-thread solver needs the FFT on both axes of a 2-D grid); the
-// fastest is kept, the FFT winning anything within 25%: a system with a
-// matrix-core axis takes its whole batch to the 256-thread instance (10
-// systems of 15^2 to 127^2, FP32 preconditioner: 10.7 ms for the two 15^2 axes
-// that were 17% faster alone, 2.9 ms with the FFT everywhere), and the FFT wins
-// alone from 31^2 up (63^2 FP64 1.31 against 1.64 ms).  Timing the solver
-// itself, one launch per solve, charges each engine with what it costs in
-// the iteration (transform, staging, occupancy) rather than in stand-alone
-// transform passes.  Runs on p's workspaces; the caller then sets the
-// chosen engines and rewrites p's descriptor and schedule.
-csl_status tune_engines(csl_problem p, int elig, int req, hipStream_t s, int *best_mask) {
-  *best_mask = req;
+// (the 512-thread solver needs the FFT on both axes of a 2-D grid).  The
+// problem's own solves keep the fastest, the FFT winning anything within 2%
+// (30 steps of 15 x 15 x 255 FP64: 1.93 ms with the matrix cores on the first
+// axis, 2.35 with the FFT; 15^2 0.59 and 0.72; 63^2 1.14 and 0.86).  Batches take the matrix cores
+// only where they are faster by 25%, because one such axis takes the whole batch
+// to the 256-thread instance (10 systems of 15^2 to 127^2, FP32 preconditioner:
+// 10.7 ms for two 15^2 axes that were 17% faster alone, 2.9 ms with the FFT
+// everywhere).  Timing the solver itself, one launch per solve, charges each
+// engine with what it costs in the iteration (transform, staging, occupancy)
+// rather than in stand-alone transform passes.  Runs on p's workspaces; the
+// caller then sets the chosen engines and rewrites p's descriptor and schedule.
+csl_status tune_engines(csl_problem p, int elig, int req, hipStream_t s, Engines *best) {
+  *best = Engines{req, req};
   hipEvent_t e0 = nullptr, e1 = nullptr;
   HIPCHK(hipEventCreate(&e0));
   if (hipEventCreate(&e1) != hipSuccess) {
@@ -683,14 +701,15 @@ csl_status tune_engines(csl_problem p, int elig, int req, hipStream_t s, int *be
   const SolveParams P = make_params(1e-300, 6, 0, 0, p->wall_khz);
   const IOPtr io0{p->gtmp, p->ytmp};
   const int reps = 3;
-  float best = INFINITY;
+  float own = INFINITY, batch = INFINITY;   // times of the engines kept
   csl_status st = CSL_OK;
   for (int mask = 0; mask < 8 && err == hipSuccess && st == CSL_OK; ++mask) {
     if ((mask & ~elig) || (mask & req) != req) continue;
     SysDesc h = h_in;
-    for (int ax = 0; ax < 3; ++ax) h.gemm[ax] = (mask >> ax) & 1;
+    set_engines(h, mask, 1);
     p->h = h;
     p->h0 = h;
+    p->own_mask = mask;
     p->smem0 = smem_in;
     p->wg512_ok = fft_everywhere(h);
     st = configure_single(p, 0, 0, 0, s);
@@ -709,9 +728,14 @@ csl_status tune_engines(csl_problem p, int elig, int req, hipStream_t s, int *be
     if (err == hipSuccess) err = hipEventSynchronize(e1);
     float ms = 0.f;
     if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
-    if (err == hipSuccess && (mask == req ? ms < best : ms < 0.75f * best)) {
-      best = ms;
-      *best_mask = mask;
+    if (err != hipSuccess) continue;
+    if (mask == req || ms < 0.98f * own) {
+      own = ms;
+      best->own = mask;
+    }
+    if (mask == req || ms < 0.75f * batch) {
+      batch = ms;
+      best->batch = mask;
     }
   }
   (void)hipEventDestroy(e0);
@@ -876,11 +900,10 @@ int csl_version(void) { return 200; }
 
 const char *csl_last_error(void) { return g_err.c_str(); }
 
-// forced_mask >= 0: the matrix-core axes are given (problem_clone), no
-// engine selection
+// forced: the matrix-core axes are given (problem_clone), no engine selection
 static csl_status create_problem_impl(const csl_grid *grid, const double *a_nodal, double alpha,
                                       double beta, const csl_problem_opts *opts, hipStream_t s,
-                                      csl_problem *out, int forced_mask) {
+                                      csl_problem *out, const Engines *forced) {
   if (!out) return fail(CSL_ERR_ARG, "out is NULL");
   *out = nullptr;
   if (!grid || !a_nodal) return fail(CSL_ERR_ARG, "grid or coefficient is NULL");
@@ -1128,11 +1151,11 @@ static csl_status create_problem_impl(const csl_grid *grid, const double *a_noda
     return fail(CSL_ERR_ARG, "an axis with n + 1 not a power of two needs the dense sine-matrix "
                              "transform (dst_engine auto or gemm)");
   }
-  int mask = req;
-  if (forced_mask >= 0) {
-    mask = forced_mask & elig;
+  Engines eng{req, req};
+  if (forced) {
+    eng = Engines{forced->own & elig, forced->batch & elig};
   } else if (o.dst_engine == CSL_DST_GEMM || g16) {
-    mask = elig;
+    eng = Engines{elig, elig};
   } else if (o.dst_engine == CSL_DST_AUTO && elig != req) {
     const ShapeKey key{dev, h.d, h.n[0], h.n[1], h.n[2], h.prec};
     bool have = false;
@@ -1140,26 +1163,29 @@ static csl_status create_problem_impl(const csl_grid *grid, const double *a_noda
       std::lock_guard<std::mutex> lk(g_engine_mu);
       auto it = g_engine_cache.find(key);
       if (it != g_engine_cache.end()) {
-        mask = it->second;
+        eng = it->second;
         have = true;
       }
     }
     if (!have) {
-      const csl_status st = tune_engines(p, elig, req, s, &mask);
+      const csl_status st = tune_engines(p, elig, req, s, &eng);
       if (st != CSL_OK) {
         free_problem(p);
         return st;
       }
       std::lock_guard<std::mutex> lk(g_engine_mu);
-      g_engine_cache[key] = mask;
+      g_engine_cache[key] = eng;
     }
   }
-  for (int ax = 0; ax < 3; ++ax) p->h.gemm[ax] = ((mask >> ax) & 1) ? (g16 ? 2 : 1) : 0;
+  set_engines(p->h, eng.batch, g16 ? 2 : 1);
   PCHK(hipMemcpyAsync(p->d_desc, &p->h, sizeof(SysDesc), hipMemcpyHostToDevice, s));
   PCHK(hipStreamSynchronize(s));
   p->h0 = p->h;
   p->smem0 = p->smem;
   p->wg512_ok = fft_everywhere(p->h);
+  p->own_mask = eng.own;
+  p->grid = *grid;
+  p->opts = o;
   {
     const csl_status st = configure_single(p, 0, 0, 0, s);
     if (st != CSL_OK) {
@@ -1168,15 +1194,13 @@ static csl_status create_problem_impl(const csl_grid *grid, const double *a_noda
     }
   }
 #undef PCHK
-  p->grid = *grid;
-  p->opts = o;
   *out = p;
   return CSL_OK;
 }
 
 csl_status create_problem(const csl_grid *grid, const double *a_nodal, double alpha, double beta,
                           const csl_problem_opts *opts, hipStream_t s, csl_problem *out) {
-  return create_problem_impl(grid, a_nodal, alpha, beta, opts, s, out, -1);
+  return create_problem_impl(grid, a_nodal, alpha, beta, opts, s, out, nullptr);
 }
 
 csl_status problem_clone(csl_problem p, hipStream_t s, csl_problem *out) {
@@ -1186,10 +1210,9 @@ csl_status problem_clone(csl_problem p, hipStream_t s, csl_problem *out) {
   csl_problem_opts o = p->opts;
   o.abar_rule = CSL_ABAR_GIVEN;   // the same abar, whichever rule produced it
   o.abar = p->h.abar;
-  int mask = 0;
-  for (int ax = 0; ax < 3; ++ax) mask |= (p->h.gemm[ax] ? 1 : 0) << ax;
+  const Engines eng{p->own_mask, engine_mask(p->h0)};
   csl_problem q = nullptr;
-  csl_status st = create_problem_impl(&p->grid, p->h.a, p->h.alpha, p->h.beta, &o, s, &q, mask);
+  csl_status st = create_problem_impl(&p->grid, p->h.a, p->h.alpha, p->h.beta, &o, s, &q, &eng);
   if (st != CSL_OK) return st;
   q->single_te = p->single_te;
   st = configure_single(q, p->tile_points, p->lds_bytes, p->block_threads, s);
@@ -1542,20 +1565,22 @@ csl_status problem_tune(csl_problem p, const double *f, double *z, csl_batch_tun
   if (f == z) return fail(CSL_ERR_ARG, "problem_tune: f and z must not alias");
   const int tp0 = p->tile_points, lds0 = p->lds_bytes, wg0 = p->block_threads,
             te0 = p->single_te;
-  // engine sets: the creation-time one and, where the engines were chosen
+  // engine sets: the one in force and, where the engines were chosen
   // automatically, the FFT on every axis that has one: the creation-time
   // timing runs the default schedule, under which a matrix-core axis can
   // win and then lose once both are tuned
-  int mask0 = 0, req = 0;
-  for (int ax = 0; ax < p->h.d; ++ax) {
-    if (p->h0.gemm[ax]) mask0 |= 1 << ax;
+  const int mask0 = engine_mask(p->h), batch0 = engine_mask(p->h0);
+  int req = 0;
+  for (int ax = 0; ax < p->h.d; ++ax)
     if (gemm_required(p->h.n[ax])) req |= 1 << ax;
-  }
   const int nmask = (p->opts.dst_engine == CSL_DST_AUTO && mask0 != req) ? 2 : 1;
   const int masks[2] = {mask0, req};
   const int gcode = p->opts.dst_engine == CSL_DST_GEMM16 ? 2 : 1;
-  auto set_mask = [&](int m) {
-    for (int ax = 0; ax < 3; ++ax) p->h0.gemm[ax] = p->h.gemm[ax] = ((m >> ax) & 1) ? gcode : 0;
+  // own: the engines of the problem's own solves; batch: those of later batches,
+  // which follow where the FFT is found the faster
+  auto set_masks = [&](int own, int batch) {
+    p->own_mask = own;
+    set_engines(p->h0, batch, gcode);
     p->wg512_ok = fft_everywhere(p->h0);
   };
   struct Cand {
@@ -1601,7 +1626,7 @@ csl_status problem_tune(csl_problem p, const double *f, double *z, csl_batch_tun
   int best_tp = tp0, best_lds = lds0, best_wg = wg0, best_te = te0, best_mask = mask0, timed = 0;
   csl_status st = CSL_OK;
   for (size_t c = 0; c < cands.size() && st == CSL_OK; ++c) {
-    set_mask(cands[c].mask);
+    set_masks(cands[c].mask, cands[c].mask);
     p->single_te = cands[c].te;
     st = configure_single(p, cands[c].tp, cands[c].lds, cands[c].wg, s);
     if (st == CSL_ERR_ARG && cands[c].te > 0) {   // more chunks than partial-sum slots
@@ -1637,7 +1662,7 @@ csl_status problem_tune(csl_problem p, const double *f, double *z, csl_batch_tun
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  set_mask(best_mask);
+  set_masks(best_mask, best_mask == req ? req : batch0);
   p->single_te = best_te;
   const csl_status st2 = configure_single(p, best_tp, best_lds, best_wg, s);
   if (st != CSL_OK) return st;
@@ -1775,7 +1800,7 @@ csl_status batch_create(const csl_problem *problems, int count, const csl_batch_
   for (int i = 0; i < count; ++i) {
     b->wg512_ok = b->wg512_ok && problems[i]->wg512_ok;
     b->all2d = b->all2d && problems[i]->h.d == 2;
-    b->g16 = b->g16 || has_gemm16(problems[i]->h);
+    b->g16 = b->g16 || has_gemm16(problems[i]->h0);
     b->plane_ok = b->plane_ok && plane_ok(problems[i]->h0) && (problems[i]->h0.prec == 0) == b->p64;
   }
   if (o.block_threads == 512 && !b->wg512_ok)
