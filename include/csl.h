@@ -180,9 +180,10 @@ csl_status problem_info(csl_problem p, double *abar, double *a_min,
  * tile_points grid points per scheduling tile (0 = about one tile per
  * workgroup and phase, which lets a single solve fill the device; 1 = one
  * LDS chunk per tile), the LDS line budget (0 or 32768 = default, 65536
- * = 64 KiB; 512 threads always hold 64 KiB of lines) and the workgroup size
- * of the persistent solver, block_threads: 0 = 512 where allowed, else 256; 256; 512, which is allowed for problems
- * whose sine transforms all run on the FFT (CSL_ERR_ARG otherwise); or 1024,
+ * = 64 KiB; 512 and 1024 threads always hold 64 KiB of lines) and the workgroup
+ * size of the persistent solver, block_threads: 0 = 512 where allowed, else 256;
+ * 256; 512, for problems whose sine transforms all run on the FFT, or were chosen
+ * automatically with the FFT for batches (CSL_ERR_ARG otherwise); or 1024,
  * the plane phase, for 3-D problems with the FFT on every axis and n0, n1
  * <= 127 (CSL_ERR_ARG otherwise): one workgroup per CU holds the real or
  * the imaginary part of a plane of axes 0 and 1 in LDS and applies the
@@ -299,7 +300,8 @@ typedef struct csl_batch_opts {
     int lds_bytes;          /* LDS line budget per workgroup: 0 = per
                                problem (32 KiB unless lines of 2048 need
                                64), 65536 = 64 KiB for every problem (twice
-                               the lines per strided tile); 32768 = 0      */
+                               the lines per strided tile); 32768 = 0; 512
+                               and 1024 threads always hold 64 KiB         */
     int block_threads;      /* workgroup size of the persistent solver: 0 =
                                512 if every problem allows it (the FFT on
                                every axis), else 256; 256; 512 (CSL_ERR_ARG

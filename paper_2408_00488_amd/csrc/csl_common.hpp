@@ -148,7 +148,8 @@ constexpr int kFlatOwn = 16;
 // Team phases: LDS of the line buffers (4096 FP64 points in up to 64 lines, and
 // one 16-byte element of padding a line) and of the workgroup (the twiddles of
 // both precisions behind them), lanes per line, lines a workgroup of 512
-// threads holds, and the column stride.  Two workgroups fit a CU.
+// threads holds, and the column stride.  The kernels run one workgroup a CU (its
+// registers, not its LDS, allow no second).
 constexpr int kTeamBufBytes = 65536 + 1024;
 constexpr int kTeamLds64Bytes = kTeamBufBytes + 512 * 16;   // FP64 alone
 constexpr int kTeamLdsBytes = kTeamLds64Bytes + 512 * 8;

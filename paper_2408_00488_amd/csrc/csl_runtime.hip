@@ -591,7 +591,8 @@ void free_problem(csl_problem p) {
 hipError_t launch_pinv_all(csl_problem p, const double2 *x, double2 *y, hipStream_t s) {
   const SysDesc &h = p->h0;   // the creation-time tiling, whatever the solver's schedule
   // FP64 with the FFT on every axis: the team passes (255^3: 0.67 ms against
-  // 1.04 in the chunked ones; faster at every size, see there)
+  // 1.04 in the chunked ones, 31^2 17 against 22 us; about even below, 15^2 16
+  // against 14), whose error is smaller at every size
   if (!h.prec && fft_everywhere(h)) return pinv512::launch_pinv(p->d_desc0, h, p->cus, x, y, s);
   const int nrow = (h.rows + h.lpt_z - 1) / h.lpt_z;
   const int pass[5] = {0, 1, 2, 3, 4};

@@ -22,10 +22,10 @@
 //     (Y_m + Y_{T-m}) / 2, S_1 = Y_0 / 2.  So a lane holds 8 values where the
 //     whole extension takes 16.  The running sum's rounding grows with the
 //     square root of its length: with the whole line combined P^{-1} was off by
-//     1.9e-14 at 1023^2 (odd extension: 0.9e-15); over T / 2 <= 64 terms of an
-//     eighth of the outputs, closed by S_{T-1} = -Y_{T/2} / 2, it is 1.0e-15
-//     (511^2: 0.9e-15 against 1.0e-15).  255^3: 73.4 -> 72.5 ms, 1023^2: 1.60 ->
-//     1.58 ms.  In FP32 the sum would show (1.5e-7 against 1.1e-7 a transform
+//     1.9e-14 at 1023^2; over T / 2 <= 64 terms of an eighth of the outputs,
+//     closed by S_{T-1} = -Y_{T/2} / 2, and with the inverse factor rounded down
+//     (team_cf) it is 5.8e-16 at 1023 x 15 (odd extension 8.5e-16), 5.3e-16 at
+//     255^2 (9.6e-16).  255^3: 73.4 -> 72.5 ms, 1023^2: 1.60 -> 1.58 ms.  In FP32 the sum would show (1.5e-7 against 1.1e-7 a transform
 //     of 511 points), for no time gained, so FP32 takes the extension.
 //
 // The vectors Tq, Tv and T are stored column by column: element (row, c) at
@@ -79,14 +79,11 @@ template <> __device__ __forceinline__ int swz<double>(int p) { return p ^ ((p >
 template <> __device__ __forceinline__ int swz<float>(int p) { return p ^ ((p >> 4) & 15); }
 
 // Points of a lane whose operands are in flight together: the stencil of K_X,
-// the recurrence of the first strided pass, the paired update of K_Z.  Twice
-// as many where a wave has 256 registers (two waves a SIMD).
-constexpr int UX = CSL_WAVES_PER_EU <= 2 ? 4 : 2;
-constexpr int UY = CSL_WAVES_PER_EU <= 2 ? 8 : 4;
-constexpr int UZ = CSL_WAVES_PER_EU <= 2 ? 4 : 2;
-// Operands of what follows a transform (the modes' eigenvalues, the first of
-// the paired update) are loaded before it where the registers hold them.
-constexpr bool kTeamEarly = CSL_WAVES_PER_EU <= 2;
+// the recurrence of the first strided pass, the paired update of K_Z (two waves
+// a SIMD, 256 registers each).
+constexpr int UX = 4;
+constexpr int UY = 8;
+constexpr int UZ = 4;
 
 struct Team {
   int n, N, lgT, T;
@@ -706,7 +703,7 @@ __device__ __forceinline__ void tile_TY(const SysDesc &S, const Ctl *C, int kind
       const int base = D == 2 ? line * ld : c * ld + (line - c * S.n[0]) * n;
       R mu[8], m1 = 0;
       if constexpr (D == 2) {
-        if (kTeamEarly) team_mu0<R>(S, t, mu);
+        team_mu0<R>(S, t, mu);   // ahead of the transform that it follows
         m1 = mode_mu<R>(S, 1)[c];
       }
       if (!first) {
@@ -751,7 +748,6 @@ __device__ __forceinline__ void tile_TY(const SysDesc &S, const Ctl *C, int kind
       team_dst(lb, smem, t, o, kind == K_Y1I);
       if constexpr (D == 2) {
         team_sync(t);
-        if (!kTeamEarly) team_mu0<R>(S, t, mu);
         gacc += team_scale<R>(S, lb, t, o, mu, act, [&](R m0) { return m0 + m1; });
         team_dst(lb, smem, t, o, true);
       }
@@ -809,12 +805,11 @@ __device__ __forceinline__ void tile_TY0(const SysDesc &S, int tile, char *smem,
     if (on) {
       Cx<R> o[8];
       R mu[8];
-      if (kTeamEarly) team_mu0<R>(S, t, mu);
+      team_mu0<R>(S, t, mu);
       const R m1 = mode_mu<R>(S, 1)[min(i1b + t.g, n1 - 1)];
       const R m2 = mode_mu<R>(S, 2)[c];
       team_dst(lb, smem, t, o, false);
       team_sync(t);
-      if (!kTeamEarly) team_mu0<R>(S, t, mu);
       gacc += team_scale<R>(S, lb, t, o, mu, act, [&](R m0) { return (m0 + m1) + m2; });
       team_dst(lb, smem, t, o, true);
       team_sync(t);
@@ -947,7 +942,7 @@ __device__ __forceinline__ void tile_TZ(const SysDesc &S, const Ctl *C, const IO
           x[u] = ldg(X + p);
         }
       };
-      if (kTeamEarly && mode == ZM_PAIR) load(0);
+      if (mode == ZM_PAIR) load(0);   // ahead of the transform
       team_dst(lb, smem, t, o, true);
       if (mode == ZM_DEFER) {
         if (act) {
@@ -974,7 +969,7 @@ __device__ __forceinline__ void tile_TZ(const SysDesc &S, const Ctl *C, const IO
 #pragma unroll
         for (int q0 = 0; q0 < 8; q0 += UZ) {
           team_fence();
-          if (!kTeamEarly || q0 > 0) load(q0);
+          if (q0 > 0) load(q0);
 #pragma unroll
           for (int u = 0; u < UZ; ++u) {
             team_fence();
