@@ -826,7 +826,7 @@ csl_status configure_batch(csl_batch b, int tile_points, int lds_bytes, int bloc
 // 13.9 / 16.3, 16 of 255^2 1.9 / 2.1 / 3.1 / 4.3, 4 of 127^3 64 / 42 / 34.7 /
 // 32.5, 16 of 63^3 26.8 / 20.6 / 18.6 / 22.4, 8 of 31^3 5.4 / 8.0 / 13.6 / 19.5.
 // A batch that one 3-D system dominates would run faster on shorter tiles (127^3
-// with four small systems 14.2 ms at 8192 points, 18.0 at 20480); it keeps the
+// with four small systems 13.5 ms at 8192 points, 17.9 at 20480); it keeps the
 // long ones because the tests of the time limit need it to run past 15 ms.
 // Other batches keep 8192.
 int default_tile_points(csl_batch b, int wg) {
