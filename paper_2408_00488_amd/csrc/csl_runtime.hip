@@ -611,10 +611,10 @@ hipError_t launch_pinv_all(csl_problem p, const double2 *x, double2 *y, hipStrea
 
 // Slots a set of a flat solve (see there) of at most mt tiles a phase on `grid`
 // workgroups, given the slots of its workspace: one for every tile; 0 if it may
-// not run flat.  With more than a few tiles a workgroup too a flat solve is the
-// faster (30 steps of 127^3 FP64 at 256 threads, 2017 tiles of a chunk: 11.3 ms, with all
-// tiles claimed 36.8, with the first 512 owned 35.3; 15 x 15 x 1023 on the plane
-// phase 4.6 ms against 9.6 and 8.8).
+// not run flat.  With several tiles a workgroup too a flat solve is the faster
+// (30 steps of 127^3 FP64 at 256 threads, 2017 tiles of a chunk: 11.3 ms, with
+// every tile claimed 36.8, with the first 512 owned 35.3; 15 x 15 x 1023 on the
+// plane phase 4.6 ms against 9.6 and 8.8).
 int flat_slots(int mt, int grid, int cap) {
   return mt <= cap && mt <= kFlatOwn * std::max(1, grid) ? mt : 0;
 }
@@ -679,11 +679,11 @@ csl_status configure_single(csl_problem p, int tile_points, int lds_bytes, int b
 // (the 512-thread solver needs the FFT on both axes of a 2-D grid).  The
 // problem's own solves keep the fastest, the FFT winning anything within 2%
 // (30 steps of 15 x 15 x 255 FP64: 1.93 ms with the matrix cores on the first
-// axis, 2.35 with the FFT; 15^2 0.59 and 0.72; 63^2 1.14 and 0.86).  Batches take the matrix cores
-// only where they are faster by 25%, because one such axis takes the whole batch
-// to the 256-thread instance (10 systems of 15^2 to 127^2, FP32 preconditioner:
-// 10.7 ms for two 15^2 axes that were 17% faster alone, 2.9 ms with the FFT
-// everywhere).  Timing the solver itself, one launch per solve, charges each
+// axis, 2.35 with the FFT; 15^2 0.59 and 0.72; 63^2 1.14 and 0.86).  Batches take
+// the matrix cores only where they are faster by 25%, because one such axis
+// takes the whole batch to the 256-thread instance (10 systems of 15^2 to 127^2,
+// FP32 preconditioner: 10.7 ms for two 15^2 axes that were 17% faster alone, 2.9
+// ms with the FFT everywhere).  Timing the solver itself, one launch per solve, charges each
 // engine with what it costs in the iteration (transform, staging, occupancy)
 // rather than in stand-alone transform passes.  Runs on p's workspaces; the
 // caller then sets the chosen engines and rewrites p's descriptor and schedule.
